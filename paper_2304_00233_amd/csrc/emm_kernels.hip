@@ -32,6 +32,7 @@
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <type_traits>
 
 namespace emm {
 
@@ -54,8 +55,8 @@ __device__ __forceinline__ float cpml_mem(float b, float psi, float a, float d) 
     return __builtin_fmaf(b, psi, a * d);
 }
 
-template <bool ST, typename T>
-__device__ __forceinline__ T ld1(const T *p) {
+template <bool ST, typename P>
+__device__ __forceinline__ auto ld1(P p) {
     if constexpr (ST) return __builtin_nontemporal_load(p);
     else return *p;
 }
@@ -113,6 +114,31 @@ __device__ void rec_dft(const StepParams &p, int blk, const float *F0,
     }
 }
 
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// Global accesses of the plane loop: (scalar 64-bit base of a plane) + (32-bit
+// byte offset of the thread's column), the pair that one load or store
+// instruction takes, so that a plane's accesses cost no vector arithmetic.
+// keep_s / keep_v stop the compiler from folding a sum of scalars into the
+// vector part and from widening a column offset ahead of the loop.
+typedef __attribute__((address_space(1))) char gchar;
+typedef __attribute__((address_space(1))) float gfloat;
+typedef __attribute__((address_space(1))) unsigned guint;
+__device__ __forceinline__ gchar *keep_s(gchar *q) {
+    asm("" : "+s"(q));
+    return q;
+}
+__device__ __forceinline__ void keep_v(unsigned &off) { asm("" : "+v"(off)); }
+template <bool ST>
+__device__ __forceinline__ float ldp(const gchar *pl, unsigned off) {
+    return ld1<ST>((const gfloat *)(pl + off));
+}
+template <bool ST>
+__device__ __forceinline__ void stp(gchar *pl, unsigned off, float v) {
+    if constexpr (ST) __builtin_nontemporal_store(v, (gfloat *)(pl + off));
+    else *(gfloat *)(pl + off) = v;
+}
+
 // ST: nontemporal hints on the updated field and dt/eps.
 // HS = false: E step (reads H, updates E, D- tables, integer-node CPML,
 //             injects J, records H channels);
@@ -127,6 +153,16 @@ __device__ void rec_dft(const StepParams &p, int blk, const float *F0,
 // buffer is rewritten only after every wave has passed the barrier that
 // follows its last use.
 //
+// Beyond the caches memory bounds it (a plain march over the same arrays with
+// no halo takes 370 us per E step on the 438 x 438 x 238 padded grid, this
+// kernel 382 per source of eight); on smaller grids the vector unit does: a
+// plane's 24 (r = 2) to 57 (r = 4) FMAs came with 116-160 other vector
+// instructions, mostly 64-bit addresses, queue shifts and bounds checks.
+// Scalar plane bases, queues that turn by renaming and halo elements clamped
+// into the array instead of branched over leave 43-78.  Per E + H step at
+// the same tiles: 8 sources at r = 4 on 400 x 400 x 200 nodes 6360 -> 6031
+// us, 128 x 128 x 96 at 9 planes per block 67 -> 56, 48^3 at 9 29.6 -> 23.8.
+//
 // CI (E step only): dt/eps comes from the compact form, one index word per
 // cell (4 bytes instead of 12) into a table of the model's distinct values,
 // held in LDS.  TX: tile width (TX x NT/TX columns per block).
@@ -136,14 +172,17 @@ __global__ __launch_bounds__(NT) void step_kernel(const StepParams p, int n_arg)
     constexpr int L = 2 * R;
     constexpr int TYS = NT / TX;
     static_assert(TX * TYS == NT && (TX & (TX - 1)) == 0, "tile of NT threads, power-of-two width");
+    static_assert(L % PF == 0, "the staged sets alternate within one turn of the z queues");
     constexpr int HL = HS ? R - 1 : R;        // halo below the own index
     constexpr int W = TX + L - 1;             // LDS row length incl. halo
     constexpr int HR = TYS + L - 1;           // LDS rows incl. halo
     constexpr int N3 = (HR * W + NT - 1) / NT;              // A3 staging loads per thread
     constexpr int N1 = ((L - 1) * TX + NT - 1) / NT;        // A1 halo loads per thread
-    __shared__ float sA3[2][HR][W];           // x and y taps
-    __shared__ float sA2[2][TYS][W];          // x taps
-    __shared__ float sA1[2][HR][TX];          // y taps
+    // each array ends in one spare word, where threads without a halo element
+    // of their own put their (unused) value
+    __shared__ float sA3[2][HR * W + 1];      // [HR][W]: x and y taps
+    __shared__ float sA2[2][TYS * W + 1];     // [TYS][W]: x taps
+    __shared__ float sA1[2][HR * TX + 1];     // [HR][TX]: y taps
     __shared__ float sCe[CI ? kCeTable : 1];
     static_assert(kCeTable <= NT, "one table entry per thread");
 
@@ -162,11 +201,13 @@ __global__ __launch_bounds__(NT) void step_kernel(const StepParams p, int n_arg)
     // neighbouring tiles of one source share their halos through L2), then
     // x, y, z chunk
     int t = xcd_tile(blk - p.nrecblk, p.nstencil);
-    const int s = tile_source(t, p.nsrc, p.nstencil, p.sorder);
-    const int bxt = t % p.xt;
+    // (integer division runs on the vector unit: say that its results are
+    // wave-uniform, so that all bases below are scalar)
+    const int s = uniform(tile_source(t, p.nsrc, p.nstencil, p.sorder));
+    const int bxt = uniform(t % p.xt);
     t /= p.xt;
-    const int byt = t % p.yt;
-    const int bzt = t / p.yt;
+    const int byt = uniform(t % p.yt);
+    const int bzt = uniform(t / p.yt);
 
     // With 64-wide tiles the row index is wave-uniform (one row per
     // wavefront); declaring it so moves the y coefficients and y-slab values
@@ -182,16 +223,12 @@ __global__ __launch_bounds__(NT) void step_kernel(const StepParams p, int n_arg)
     const bool valid = i >= R && i <= p.n1 - 1 - R && j <= p.n2 - 1 - R;
     const int jc = min(j, p.n2 - 1);
     const long long fo = (long long)s * p.fstride;   // per-block (uniform) base offset
-    A1 += fo;
-    A2 += fo;
-    A3 += fo;
-    const int plane = (int)p.plane;                   // 32-bit offsets below this base
-    const float *U1 = (HS ? p.H1 : p.E1) + fo;
-    const float *U2 = (HS ? p.H2 : p.E2) + fo;
-    const float *U3 = (HS ? p.H3 : p.E3) + fo;
-    float *O1 = (HS ? p.H1 : p.Eo1) + fo;     // updated field (E may go out of place)
-    float *O2 = (HS ? p.H2 : p.Eo2) + fo;
-    float *O3 = (HS ? p.H3 : p.Eo3) + fo;
+    const long long pb = p.plane * (long long)sizeof(float);   // bytes per plane
+    // the three components of a field lie cs bytes apart
+    const long long cs = (long long)p.nsrc * p.fstride * (long long)sizeof(float);
+    gchar *const A = (gchar *)(A1 + fo);                       // the field that is read
+    gchar *const U = (gchar *)((HS ? p.H1 : p.E1) + fo);       // the updated field: old values
+    gchar *const O = (gchar *)((HS ? p.H1 : p.Eo1) + fo);      // and new (E may go out of place)
 
     const float *tx_ = HS ? p.cpx : p.cmx;
     const float *ty_ = HS ? p.cpy : p.cmy;
@@ -209,79 +246,89 @@ __global__ __launch_bounds__(NT) void step_kernel(const StepParams p, int n_arg)
     const bool xs = valid && (i < nb || i > p.n1 - 1 - nb);
     const bool ys = valid && (j < nb || j > p.n2 - 1 - nb);
     float ax = 0.f, bx = 0.f, ay = 0.f, by = 0.f;
-    int ix = 0, jy = 0;
+    unsigned ox = 0, oy = 0;                  // byte offsets of the column in a plane of the x / y memories
     if (xs) {
         ax = (HS ? p.axh : p.axi)[i];
         bx = (HS ? p.bxh : p.bxi)[i];
-        ix = i < nb ? i : i - (p.n1 - nb2);
+        ox = 4u * (unsigned)(j * nb2 + (i < nb ? i : i - (p.n1 - nb2)));
     }
     if (ys) {
         ay = (HS ? p.ayh : p.ayi)[j];
         by = (HS ? p.byh : p.byi)[j];
-        jy = j < nb ? j : j - (p.n2 - nb2);
+        oy = 4u * (unsigned)((j < nb ? j : j - (p.n2 - nb2)) * p.pitch + i);
     }
     const float *az_ = HS ? p.azh : p.azi;
     const float *bz_ = HS ? p.bzh : p.bzi;
-    float *px0 = p.psx0 + s * p.psxs, *px1 = p.psx1 + s * p.psxs;
-    float *py0 = p.psy0 + s * p.psys, *py1 = p.psy1 + s * p.psys;
-    float *pz0 = p.psz0 + s * p.pszs, *pz1 = p.psz1 + s * p.pszs;
-    const float *ce1 = p.ce1, *ce2 = p.ce2, *ce3 = p.ce3;
+    // memories of the first derivative of each axis; the second's lie behind all sources'
+    gchar *const px = (gchar *)(p.psx0 + s * p.psxs), *const py = (gchar *)(p.psy0 + s * p.psys),
+          *const pz = (gchar *)(p.psz0 + s * p.pszs);
+    auto xmem = [&](int k) { return keep_s(px + k * (4ll * p.n2 * nb2)); };
+    auto ymem = [&](int k) { return keep_s(py + k * (4ll * nb2 * p.pitch)); };
+    auto zmem = [&](int k) { return keep_s(pz + (k < nb ? k : k - (p.n3 - nb2)) * pb); };
+    const long long x1 = 4 * p.nsrc * p.psxs, y1 = 4 * p.nsrc * p.psys, z1 = 4 * p.nsrc * p.pszs;
     // read only after the first barrier of the plane loop
     if (CI && (int)threadIdx.x < p.ncet) sCe[threadIdx.x] = p.cet[threadIdx.x];
 
-    // dipole source of this block's source (E step only)
-    int scomp = -1, sbx = 0, sby = 0, sbz = 0;
+    // dipole source of this block's source (E step only): its planes, and
+    // this column's position in the stencil (or outside)
+    int scomp = -1, sbz = 0, sq0 = -1;
     float sn = 0.f;
     const float *sq = nullptr;
     if (!HS) {
         scomp = p.src_info[4 * s];
-        sbx = p.src_info[4 * s + 1];
-        sby = p.src_info[4 * s + 2];
+        const int sbx = p.src_info[4 * s + 1], sby = p.src_info[4 * s + 2];
         sbz = p.src_info[4 * s + 3];
         sn = p.wavelet[n];
         sq = p.src_q + (long long)s * L * L * L;
+        if (j >= sby && j < sby + L && i >= sbx && i < sbx + L) sq0 = (j - sby) * L + (i - sbx);
     }
 
     // Staging map (identical for every plane): element e of the A3 tile is
     // row e / W, column e % W of the LDS tile, i.e. global (j0 - HL + row,
-    // i0 - HL + col); out-of-array elements stage zeros.
+    // i0 - HL + col).  Elements off the array are only read by threads whose
+    // cell is not updated, so they load the nearest element of the array.
     // (LDS index of A3 element u: tid + u * NT; of A1 halo element u: row
     // ly1(u) * TX + tx.)
-    int o3[N3];        // plane offset, or -1 (outside the array or the tile)
+    auto at = [&](int gj, int gi) {
+        return 4u * (unsigned)(min(max(gj, 0), p.n2 - 1) * p.pitch + min(max(gi, 0), p.pitch - 1));
+    };
+    unsigned o3[N3], o1[N1], o2;              // byte offsets in the plane
 #pragma unroll
     for (int u = 0; u < N3; ++u) {
         const int e = tid + u * NT;
         const int ly = e / W, lx = e - ly * W;
-        const int gj = j0 - HL + ly, gi = i0 - HL + lx;
-        o3[u] = (e < HR * W && gj >= 0 && gj < p.n2 && gi >= 0 && gi < p.pitch) ? gj * p.pitch + gi : -1;
+        o3[u] = e < HR * W ? at(j0 - HL + ly, i0 - HL + lx) : at(j0, i0);
     }
+    const int l3 = tid + (N3 - 1) * NT < HR * W ? tid + (N3 - 1) * NT : HR * W;     // last element's LDS index
     auto ly1 = [&](int u) {
         const int hy = (tid + u * NT) / TX;
         return hy < HL ? hy : TYS + hy;
     };
-    int o1[N1];
 #pragma unroll
-    for (int u = 0; u < N1; ++u) {
-        const int e = tid + u * NT;
-        const int gj = j0 - HL + ly1(u);
-        o1[u] = (e < (L - 1) * TX && gj >= 0 && gj < p.n2) ? gj * p.pitch + i0 + tx : -1;
-    }
-    int o2 = -1, l2 = -1;
-    if (tid < TYS * (L - 1)) {
+    for (int u = 0; u < N1; ++u)
+        o1[u] = tid + u * NT < (L - 1) * TX ? at(j0 - HL + ly1(u), i0 + tx) : at(j0, i0);
+    const int l1 = tid + (N1 - 1) * NT < (L - 1) * TX ? ly1(N1 - 1) * TX + tx : HR * TX;
+    int l2;
+    {
         const int hy = tid / (L - 1), hx = tid % (L - 1);
         const int lx = hx < HL ? hx : TX + hx;
-        const int gi = i0 - HL + lx, gj = min(j0 + hy, p.n2 - 1);
-        l2 = hy * W + lx;
-        o2 = (gi >= 0 && gi < p.pitch) ? gj * p.pitch + gi : -1;
+        const bool has = tid < TYS * (L - 1);
+        l2 = has ? hy * W + lx : TYS * W;
+        o2 = has ? at(j0 + hy, i0 - HL + lx) : at(j0, i0);
     }
-    const int own = jc * p.pitch + i;          // plane offset of this thread's column
+    unsigned own = 4u * (unsigned)(jc * p.pitch + i);    // byte offset of this thread's column in a plane
 
-    // z queues of the two z-differentiated components: planes k-HL .. k-HL+L-1
+    // z queues of the two z-differentiated components: planes k - HL ..
+    // k - HL + L - 1 of step k; plane k - HL + m sits at index (k - k0 + m) % L,
+    // so that the queues turn by renaming (the plane loop is unrolled L times)
     float q1[L], q2[L];
+    q1[L - 1] = q2[L - 1] = 0.f;
 #pragma unroll
     for (int m = 0; m < L - 1; ++m) {
-        q1[m] = A1[(unsigned)((k0 - HL + m) * plane + own)];
-        q2[m] = A2[(unsigned)((k0 - HL + m) * plane + own)];
+        gchar *a = keep_s(A + (k0 - HL + m) * pb);
+        keep_v(own);
+        q1[m] = ldp<false>(a, own);
+        q2[m] = ldp<false>(keep_s(a + cs), own);
     }
 
     // staged registers of a plane in flight (fields, dt/eps and the CPML
@@ -293,70 +340,74 @@ __global__ __launch_bounds__(NT) void step_kernel(const StepParams p, int n_arg)
         float mxn0, mxn1, myn0, myn1, mzn0, mzn1;
         unsigned cin;
     };
+    auto zslab = [&](int k) { return k < nb || k > p.n3 - 1 - nb; };
     auto issue = [&](Stage &S, int k) {
-        float(&f3)[N3] = S.f3;
-        float(&f1)[N1] = S.f1;
-        float &f2 = S.f2, &e1n = S.e1n, &e2n = S.e2n, &un1 = S.un1, &un2 = S.un2, &un3 = S.un3;
-        float &cn1 = S.cn1, &cn2 = S.cn2, &cn3 = S.cn3, &mxn0 = S.mxn0, &mxn1 = S.mxn1;
-        float &myn0 = S.myn0, &myn1 = S.myn1, &mzn0 = S.mzn0, &mzn1 = S.mzn1;
-        unsigned &cin = S.cin;
-        const int pk = k * plane;
+        const long long kb = k * pb;
+        keep_v(own);
+        keep_v(o2);
 #pragma unroll
-        for (int u = 0; u < N3; ++u) f3[u] = o3[u] >= 0 ? A3[(unsigned)(pk + o3[u])] : 0.f;
+        for (int u = 0; u < N3; ++u) keep_v(o3[u]);
 #pragma unroll
-        for (int u = 0; u < N1; ++u) f1[u] = o1[u] >= 0 ? A1[(unsigned)(pk + o1[u])] : 0.f;
-        if (o2 >= 0) f2 = A2[(unsigned)(pk + o2)];
-        const unsigned ge = (unsigned)((k - HL + L - 1) * plane + own);
-        e1n = A1[ge];
-        e2n = A2[ge];
-        if (valid) {
-            if (xs) {
-                const unsigned id = (unsigned)((k * p.n2 + j) * nb2 + ix);
-                mxn0 = px0[id];
-                mxn1 = px1[id];
-            }
-            if (ys) {
-                const unsigned id = (unsigned)((k * nb2 + jy) * p.pitch + i);
-                myn0 = py0[id];
-                myn1 = py1[id];
-            }
-            if (k < nb || k > p.n3 - 1 - nb) {
-                const int kz = k < nb ? k : k - (p.n3 - nb2);
-                const unsigned id = (unsigned)((kz * p.n2 + j) * p.pitch + i);
-                mzn0 = pz0[id];
-                mzn1 = pz1[id];
-            }
-            const unsigned g = (unsigned)(pk + own);
-            un1 = ld1<ST>(&U1[g]);
-            un2 = ld1<ST>(&U2[g]);
-            un3 = ld1<ST>(&U3[g]);
-            if (!HS && CI) {
-                cin = ld1<ST>(&p.cei[g]);
-            } else if (!HS) {
-                cn1 = ld1<ST>(&ce1[g]);
-                cn2 = ld1<ST>(&ce2[g]);
-                cn3 = ld1<ST>(&ce3[g]);
-            }
+        for (int u = 0; u < N1; ++u) keep_v(o1[u]);
+        gchar *a = keep_s(A + kb);
+#pragma unroll
+        for (int u = 0; u < N1; ++u) S.f1[u] = ldp<false>(a, o1[u]);
+        a = keep_s(a + cs);
+        S.f2 = ldp<false>(a, o2);
+        a = keep_s(a + cs);
+#pragma unroll
+        for (int u = 0; u < N3; ++u) S.f3[u] = ldp<false>(a, o3[u]);
+        a = keep_s(A + kb + (L - 1 - HL) * pb);
+        S.e1n = ldp<false>(a, own);
+        S.e2n = ldp<false>(keep_s(a + cs), own);
+        a = keep_s(U + kb);
+        S.un1 = ldp<ST>(a, own);
+        a = keep_s(a + cs);
+        S.un2 = ldp<ST>(a, own);
+        S.un3 = ldp<ST>(keep_s(a + cs), own);
+        if (!HS && CI) {
+            S.cin = ld1<ST>((const guint *)(keep_s((gchar *)p.cei + kb) + own));
+        } else if (!HS) {
+            S.cn1 = ldp<ST>(keep_s((gchar *)p.ce1 + kb), own);
+            S.cn2 = ldp<ST>(keep_s((gchar *)p.ce2 + kb), own);
+            S.cn3 = ldp<ST>(keep_s((gchar *)p.ce3 + kb), own);
+        }
+        if (xs) {
+            keep_v(ox);
+            gchar *m = xmem(k);
+            S.mxn0 = ldp<false>(m, ox);
+            S.mxn1 = ldp<false>(keep_s(m + x1), ox);
+        }
+        if (ys) {
+            keep_v(oy);
+            gchar *m = ymem(k);
+            S.myn0 = ldp<false>(m, oy);
+            S.myn1 = ldp<false>(keep_s(m + y1), oy);
+        }
+        if (zslab(k)) {
+            keep_v(own);
+            gchar *m = zmem(k);
+            S.mzn0 = ldp<false>(m, own);
+            S.mzn1 = ldp<false>(keep_s(m + z1), own);
         }
     };
-    auto step = [&](Stage &S, int k) {
-        const int b = (k - k0) & 1;
-        const float(&f3)[N3] = S.f3;
-        const float(&f1)[N1] = S.f1;
-        const float f2 = S.f2;
-        q1[L - 1] = S.e1n;
-        q2[L - 1] = S.e2n;
-        float *s3 = &sA3[b][0][0];
+    // plane k, the V-th (mod L) of this chunk
+    auto step = [&](Stage &S, int k, auto turn) {
+        constexpr int V = decltype(turn)::value, B = V & 1;
+        q1[(V + L - 1) % L] = S.e1n;
+        q2[(V + L - 1) % L] = S.e2n;
+        const cfloat *czp = uniform_table(tz_ + k * L);
+        float cz[L];
 #pragma unroll
-        for (int u = 0; u < N3; ++u)
-            if (u < N3 - 1 || tid + u * NT < HR * W) s3[tid + u * NT] = f3[u];
-        float *s1 = &sA1[b][0][0];
+        for (int m = 0; m < L; ++m) cz[m] = czp[m];
+        float *s3 = sA3[B], *s1 = sA1[B], *s2 = sA2[B];
 #pragma unroll
-        for (int u = 0; u < N1; ++u)
-            if (u < N1 - 1 || tid + u * NT < (L - 1) * TX) s1[ly1(u) * TX + tx] = f1[u];
-        if (l2 >= 0) (&sA2[b][0][0])[l2] = o2 >= 0 ? f2 : 0.f;
-        sA2[b][ty][tx + HL] = q2[HL];
-        sA1[b][ty + HL][tx] = q1[HL];
+        for (int u = 0; u < N3; ++u) s3[u < N3 - 1 ? tid + u * NT : l3] = S.f3[u];
+#pragma unroll
+        for (int u = 0; u < N1; ++u) s1[u < N1 - 1 ? ly1(u) * TX + tx : l1] = S.f1[u];
+        s2[l2] = S.f2;
+        s2[ty * W + tx + HL] = q2[(V + HL) % L];
+        s1[(ty + HL) * TX + tx] = q1[(V + HL) % L];
         const float u1 = S.un1, u2 = S.un2, u3 = S.un3;
         const float mx0 = S.mxn0, mx1 = S.mxn1, my0 = S.myn0, my1 = S.myn1, mz0 = S.mzn0, mz1 = S.mzn1;
         float ce1 = S.cn1, ce2 = S.cn2, ce3 = S.cn3;
@@ -368,85 +419,80 @@ __global__ __launch_bounds__(NT) void step_kernel(const StepParams p, int n_arg)
             ce2 = sCe[(ci >> 8) & 255u];
             ce3 = sCe[(ci >> 16) & 255u];
         }
-
-        if (valid) {
-            const cfloat *cz = uniform_table(tz_ + k * L);
-            float d2a3 = 0.f, d2a1 = 0.f, d1a3 = 0.f, d1a2 = 0.f, d3a2 = 0.f, d3a1 = 0.f;
+        float d2a3 = 0.f, d2a1 = 0.f, d1a3 = 0.f, d1a2 = 0.f, d3a2 = 0.f, d3a1 = 0.f;
 #pragma unroll
-            for (int m = 0; m < L; ++m) {
-                d2a3 += cy[m] * sA3[b][ty + m][tx + HL];
-                d2a1 += cy[m] * sA1[b][ty + m][tx];
-                d1a3 += cx[m] * sA3[b][ty + HL][tx + m];
-                d1a2 += cx[m] * sA2[b][ty][tx + m];
-                d3a2 += cz[m] * q2[m];
-                d3a1 += cz[m] * q1[m];
-            }
-            if (xs) {
-                const unsigned id = (unsigned)((k * p.n2 + j) * nb2 + ix);
-                float v = cpml_mem(bx, mx0, ax, d1a3);
-                px0[id] = v;
-                d1a3 += v;
-                v = cpml_mem(bx, mx1, ax, d1a2);
-                px1[id] = v;
-                d1a2 += v;
-            }
-            if (ys) {
-                const unsigned id = (unsigned)((k * nb2 + jy) * p.pitch + i);
-                float v = cpml_mem(by, my0, ay, d2a3);
-                py0[id] = v;
-                d2a3 += v;
-                v = cpml_mem(by, my1, ay, d2a1);
-                py1[id] = v;
-                d2a1 += v;
-            }
-            if (k < nb || k > p.n3 - 1 - nb) {
-                const int kz = k < nb ? k : k - (p.n3 - nb2);
-                const float az = uniform_table(az_)[k], bz = uniform_table(bz_)[k];
-                const unsigned id = (unsigned)((kz * p.n2 + j) * p.pitch + i);
-                float v = cpml_mem(bz, mz0, az, d3a2);
-                pz0[id] = v;
-                d3a2 += v;
-                v = cpml_mem(bz, mz1, az, d3a1);
-                pz1[id] = v;
-                d3a1 += v;
-            }
-            float c1 = d2a3 - d3a2, c2 = d3a1 - d1a3, c3 = d1a2 - d2a1;
-            const unsigned g = (unsigned)(k * plane + own);
-            if (HS) {
-                st1<ST>(&O1[g], u1 - p.ch * c1);
-                st1<ST>(&O2[g], u2 - p.ch * c2);
-                st1<ST>(&O3[g], u3 - p.ch * c3);
-            } else {
-                if (k >= sbz && k < sbz + L && j >= sby && j < sby + L && i >= sbx && i < sbx + L) {
-                    const float jv = sn * sq[((k - sbz) * L + (j - sby)) * L + (i - sbx)];
-                    if (scomp == 0) c1 -= jv;
-                    else if (scomp == 1) c2 -= jv;
-                    else c3 -= jv;
-                }
-                st1<ST>(&O1[g], u1 + ce1 * c1);
-                st1<ST>(&O2[g], u2 + ce2 * c2);
-                st1<ST>(&O3[g], u3 + ce3 * c3);
-            }
+        for (int m = 0; m < L; ++m) {
+            d2a3 += cy[m] * s3[(ty + m) * W + tx + HL];
+            d2a1 += cy[m] * s1[(ty + m) * TX + tx];
+            d1a3 += cx[m] * s3[(ty + HL) * W + tx + m];
+            d1a2 += cx[m] * s2[ty * W + tx + m];
+            d3a2 += cz[m] * q2[(V + m) % L];
+            d3a1 += cz[m] * q1[(V + m) % L];
         }
-#pragma unroll
-        for (int m = 0; m < L - 1; ++m) {
-            q1[m] = q1[m + 1];
-            q2[m] = q2[m + 1];
+        if (xs) {
+            keep_v(ox);
+            gchar *m = xmem(k);
+            float v = cpml_mem(bx, mx0, ax, d1a3);
+            stp<false>(m, ox, v);
+            d1a3 += v;
+            v = cpml_mem(bx, mx1, ax, d1a2);
+            stp<false>(keep_s(m + x1), ox, v);
+            d1a2 += v;
+        }
+        if (ys) {
+            keep_v(oy);
+            gchar *m = ymem(k);
+            float v = cpml_mem(by, my0, ay, d2a3);
+            stp<false>(m, oy, v);
+            d2a3 += v;
+            v = cpml_mem(by, my1, ay, d2a1);
+            stp<false>(keep_s(m + y1), oy, v);
+            d2a1 += v;
+        }
+        if (zslab(k)) {
+            const float az = uniform_table(az_)[k], bz = uniform_table(bz_)[k];
+            const float v0 = cpml_mem(bz, mz0, az, d3a2), v1 = cpml_mem(bz, mz1, az, d3a1);
+            if (valid) {
+                keep_v(own);
+                gchar *m = zmem(k);
+                stp<false>(m, own, v0);
+                stp<false>(keep_s(m + z1), own, v1);
+            }
+            d3a2 += v0;
+            d3a1 += v1;
+        }
+        float c1 = d2a3 - d3a2, c2 = d3a1 - d1a3, c3 = d1a2 - d2a1;
+        if (!HS && k >= sbz && k < sbz + L && sq0 >= 0) {
+            const float jv = sn * sq[(k - sbz) * L * L + sq0];
+            if (scomp == 0) c1 -= jv;
+            else if (scomp == 1) c2 -= jv;
+            else c3 -= jv;
+        }
+        if (valid) {
+            keep_v(own);
+            gchar *o = keep_s(O + k * pb);
+            stp<ST>(o, own, HS ? u1 - p.ch * c1 : u1 + ce1 * c1);
+            o = keep_s(o + cs);
+            stp<ST>(o, own, HS ? u2 - p.ch * c2 : u2 + ce2 * c2);
+            stp<ST>(keep_s(o + cs), own, HS ? u3 - p.ch * c3 : u3 + ce3 * c3);
         }
     };
-    Stage SA = {}, SB = {};
-    issue(SA, k0);
-    int k = k0;
-    if (PF == 2) {
-        if (k0 + 1 < k1) issue(SB, k0 + 1);
-        for (; k + 1 < k1; k += 2) {
-            step(SA, k);
-            step(SB, k + 1);
+    Stage S[PF] = {};
+#pragma unroll
+    for (int f = 0; f < PF; ++f)
+        if (k0 + f < k1) issue(S[f], k0 + f);
+    // one turn of the queues per pass
+    auto turn = [&](auto self, int k, auto v) -> bool {
+        constexpr int V = decltype(v)::value;
+        if constexpr (V < L) {
+            if (k >= k1) return true;
+            step(S[V % PF], k, v);
+            return self(self, k + 1, std::integral_constant<int, V + 1>{});
+        } else {
+            return false;
         }
-        if (k < k1) step(SA, k);
-    } else {
-        for (; k < k1; ++k) step(SA, k);
-    }
+    };
+    for (int k = k0; !turn(turn, k, std::integral_constant<int, 0>{}); k += L) {}
 }
 
 // Register-blocked variant of step_kernel: a 64-wide tile of 4 RY rows,
