@@ -93,7 +93,8 @@ typedef struct {
                               (two levels); 0: planned [0] */
     int    nontemporal;    /* stencil kernels move the arrays they touch once with nontemporal
                               hints: 1 = yes, 0 = no, -1 = autotuned with tile_kz = -1, else
-                              yes when the fields and dt/eps exceed 160 MiB [-1] */
+                              yes for fewer than four sources whose fields and dt/eps exceed
+                              160 MiB [-1] */
     int    airwave;        /* 1: the first z node is the sea (or land) surface with air above it
                               (Section 3.3): no cell above it is updated and the ghost planes the
                               stencils reach are filled after each half step from 2-D Fourier
@@ -135,7 +136,7 @@ typedef struct {
                               too (0 = the most whose checkpoints fit one level, see there) [0] */
     int    tile_x;         /* columns per block of the stencil kernels: 64 (x 4 rows) or 32 (x 8
                               rows); 0 = autotuned with tile_kz = -1, else 32 where it leaves
-                              fewer idle lanes in the last x tile of a row or at rd >= 3 [0] */
+                              fewer idle lanes in the last x tile of a row [0] */
     int    tile_rows;      /* grid rows each wavefront of a stencil block updates: 1, or 2 / 4
                               (64-wide tiles of 8 / 16 rows, register-blocked: less staged halo
                               per cell, more loads per thread, but 2-3 waves per SIMD; needs
@@ -145,8 +146,9 @@ typedef struct {
                               source fastest (the blocks of all sources for one spatial tile run
                               together and share dt/eps through L2), 1 = source slowest (each XCD
                               streams whole sources, so neighbouring tiles of one source share their
-                              halos in L2); -1 = autotuned with tile_kz = -1, else 0.  Both give
-                              the same bits [-1] */
+                              halos in L2); -1 = autotuned with tile_kz = -1, else 1 for four or more
+                              sources whose fields exceed 32 MB, 0 otherwise.  Both give the same
+                              bits [-1] */
 } emm_options;
 
 /* A point electric dipole (the acquisition of Section 5): position in

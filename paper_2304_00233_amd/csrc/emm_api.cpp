@@ -259,15 +259,35 @@ int choose_kz(const emm_model *m, int xt, int yt, int nsrc) {
         auto it = m->tuned.find(nsrc);
         if (it != m->tuned.end()) return it->second.kz;
     }
-    const long long per_chunk = (long long)xt * yt * nsrc;
-    long long zc = std::max<long long>(1, (4096 + per_chunk - 1) / per_chunk);
-    zc = std::min<long long>(zc, std::max(1, nzv / 8));
+    // About 640 blocks (2.5 per CU), but 3 planes at least and not more than
+    // pays: a chunk reloads 2r - 1 planes of two components, yet short chunks
+    // keep neighbouring tiles' halos closer in time.  us a step, E + H, one
+    // source:  48^3, r = 2: 17.8 at 4, 18.7 at 3, 19.5 at 6, 21.9 at 8
+    //          20^3: 12.0 at 3, 13.4 at 4;  r = 4: 13.8 and 15.5
+    //          90 x 80 x 40, r = 4: 26.6 at 6, 29.2 at 4, 27.7 at 8
+    //          128 x 128 x 96, r = 2: 51.8 at 6, 53.2 at 7; r = 4: 67.0 at
+    //          11 and 24, 69.7 at 8; r = 3: 61.6 at 6, 62.9 at 8 and 24
+    //          41 x 174 x 87, r = 3: 45.4 at 6, 48.4 at 16; r = 2: 42.6 at
+    //          4, 44.2 at 6
+    //          256^3, r = 2: 402 at 6, 411 at 10, 431 at 22
+    //          200 x 200 x 100, r = 4, two sources: 289 at 22, 297 at 33
+    //          400 x 400 x 200, r = 4: 804 at 39, 826 at 24 (40 planes
+    //          while 4096 blocks remain)
+    const long long cols = (long long)xt * yt * nsrc;
+    auto chunks = [&](long long kz) { return std::max<long long>(1, (nzv + kz / 2) / kz); };
+    const int top = m->r <= 3 ? 6 : cols * chunks(40) >= 4096 ? 40 : 24;
+    const long long want = std::min<long long>(top, std::max<long long>(3, (cols * nzv + 320) / 640));
+    const long long zc = chunks(want);
     return (int)((nzv + zc - 1) / zc);
 }
 
 // Nontemporal hints when the arrays one step touches (fields of all sources
 // and dt/eps) exceed 160 MiB, well inside the 256 MB Infinity Cache below
-// that; the autotuner overrides this with a measurement.
+// that, but not for a batch in the source-slowest order (choose_sorder): 8
+// sources at r = 4 on 400 x 400 x 200 nodes take 6031 us a step without and
+// 6275 with hints, 4 at r = 2 on 256^3 1588 and 1612; two sources on 200 x
+// 200 x 100 at r = 4 316 without and 293 with.  The autotuner overrides this
+// with a measurement.
 int choose_stream(const emm_model *m, long long fstride, int nsrc) {
     if (m->opt.nontemporal >= 0) return m->opt.nontemporal;
     if (m->opt.tile_kz < 0) {
@@ -275,7 +295,7 @@ int choose_stream(const emm_model *m, long long fstride, int nsrc) {
         if (it != m->tuned.end()) return it->second.stream;
     }
     const double resident = (6.0 * nsrc + 3.0) * (double)fstride * sizeof(float);
-    return resident > 160.0 * (1 << 20) ? 1 : 0;
+    return nsrc < 4 && resident > 160.0 * (1 << 20) ? 1 : 0;
 }
 
 // Compact dt/eps whenever the model has it (8 of the E step's 48 B per
@@ -292,7 +312,8 @@ int choose_compact(const emm_model *m, int nsrc) {
 
 // Tile width of the step kernels (64 x 4 or 32 x 8 columns): the option,
 // the autotuner's choice, else 32 where it leaves clearly fewer idle lanes
-// in the last x tile of a row, or at r >= 3 (less y halo per cell).
+// in the last x tile of a row (128 x 128 x 96 at r = 2: 51.8 us a step with
+// 32, 54.5 with 64; 400 x 400 x 200 at r = 4: 799 with 64, 802 with 32).
 int choose_tx(const emm_model *m, int nsrc) {
     if (m->opt.tile_x > 0) return m->opt.tile_x;
     if (m->opt.tile_kz < 0) {
@@ -302,18 +323,24 @@ int choose_tx(const emm_model *m, int nsrc) {
     const int valid = m->np[0] - 2 * m->r;
     auto lanes = [&](int w) { return (m->np[0] - m->r + w - 1) / w * w; };
     const double e64 = (double)valid / lanes(64), e32 = (double)valid / lanes(32);
-    return (m->r >= 3 || e32 > e64 + 0.02) ? 32 : 64;
+    return e32 > e64 + 0.02 ? 32 : 64;
 }
 
 // Tile order of the sources: the option, the autotuner's choice, else
-// source fastest.
+// source slowest from four sources on whose fields exceed the eight 4 MB
+// L2s (each XCD streams whole sources and neighbouring tiles find their
+// halos in its L2: 8 sources at r = 4 on 400 x 400 x 200 nodes 6495 us a
+// step against 7678 source fastest, 4 at r = 2 on 256^3 1588 against 1703, 5
+// on 48^3 68 against 74), source fastest for two or three (200 x 200 x 100,
+// two sources: 289 against 293).
 int choose_sorder(const emm_model *m, int nsrc) {
     if (m->opt.src_order >= 0) return m->opt.src_order;
     if (m->opt.tile_kz < 0) {
         auto it = m->tuned.find(nsrc);
         if (it != m->tuned.end()) return it->second.sorder;
     }
-    return 0;
+    const double fields = 24.0 * nsrc * (double)m->pitch * m->np[1] * m->np[2];
+    return nsrc >= 4 && fields > 32.0 * (1 << 20) ? 1 : 0;
 }
 
 // Rows per wavefront of the step kernels: the option, the autotuner's
