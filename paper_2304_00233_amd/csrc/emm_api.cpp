@@ -130,6 +130,7 @@ struct emm_model {
     // adjoint: Et|Hb fields, Q (12 slab arrays), T (6), E snapshots, per-source
     // gradients, transposed tables, injection lists and coefficients
     DevBuf adjf, adjq, adjt, snaps, grad, grad32, tabT, inj, injA, adjcpml;
+    int snaps_nsrc = 0;                             // sources the cleared E snapshots are laid out for
     DevBuf gsum;                                    // dL/dlog sigma on the input cells, summed over sources
     // receiver injection lists of the last emm_gradient (CSR over target
     // cells, in m->inj), kept while the acquisition's receiver items, the
@@ -2155,7 +2156,14 @@ emm_status gradient_run(emm_model *m, const emm_source *src, int nsrc, const emm
     if ((st = ensure(m, m->adjf, (size_t)6 * nsrc * fstride * sizeof(float))) != EMM_OK) return st;
     if ((st = ensure(m, m->adjq, (size_t)std::max<long long>(1, 2 * nsrc * slab_src) * sizeof(float))) != EMM_OK) return st;
     if ((st = ensure(m, m->adjt, (size_t)std::max<long long>(1, nsrc * slab_src) * sizeof(float))) != EMM_OK) return st;
+    // cells off the update set are read as halo and never written: zero in
+    // every slot, so cleared when the buffer is new or its slots move
+    const void *snaps_before = m->snaps.p;
     if ((st = ensure(m, m->snaps, (size_t)(cin + 1) * 3 * nsrc * fstride * sizeof(float))) != EMM_OK) return st;
+    if (m->snaps.p != snaps_before || m->snaps_nsrc != nsrc) {
+        HIP_OK(m, hipMemsetAsync(m->snaps.p, 0, m->snaps.bytes, stream));
+        m->snaps_nsrc = nsrc;
+    }
     if (cin < ckpt &&
         (st = ensure(m, m->ickpts, (size_t)((ckpt + cin - 1) / cin) * state_floats(m) * nsrc * sizeof(float))) != EMM_OK)
         return st;
