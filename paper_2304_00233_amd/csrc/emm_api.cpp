@@ -20,6 +20,7 @@
 
 #include "emm_adjoint.h"
 #include "emm_internal.h"
+#include "emm_resident.h"
 #include "emm_setup.h"
 
 namespace {
@@ -149,6 +150,14 @@ struct emm_model {
     } injc;
     Acq acq;
     std::map<int, Tune> tuned;                      // autotuned launch choices per source count
+    // whole time loops in one launch (small grids): the tile plan (gy = 0: the
+    // grid does not qualify), mailbox, receiver samples, their sums, and a
+    // flag that a wait ran out of time
+    emm::ResidentPlan res;
+    DevBuf mail, samples, sums, stuck, rows;
+    std::vector<emm::ResidentRow> row_h[2];         // host copies of what `rows` holds
+    std::vector<int> item_rows_h[2];
+    unsigned mail_tag = 0;                          // last tag used; 0: the mailbox is to be cleared
     std::unique_ptr<emm::AirBoundary> air;          // ghost planes above the surface (airwave)
     hipEvent_t ev_loop[2] = {nullptr, nullptr};
     std::vector<hipEvent_t> ring;       // profiling: start/end pairs
@@ -446,7 +455,7 @@ void emm_destroy(emm_model *m) {
     for (float *p : m->tab) if (p) (void)hipFree(p);
     for (DevBuf *b : {&m->fields, &m->psi, &m->acc, &m->cpml, &m->srcinfo, &m->srcq, &m->wav,
                       &m->items, &m->itemw, &m->phase, &m->fieldsB, &m->psiB, &m->ckpts, &m->ickpts, &m->adjf, &m->adjq, &m->adjt,
-                      &m->snaps, &m->grad, &m->grad32, &m->tabT, &m->inj, &m->injA, &m->adjcpml, &m->stepdev})
+                      &m->snaps, &m->grad, &m->grad32, &m->tabT, &m->inj, &m->injA, &m->adjcpml, &m->stepdev, &m->gsum, &m->mail, &m->samples, &m->sums, &m->stuck, &m->rows})
         if (b->p && !b->borrowed) (void)hipFree(b->p);
     for (hipEvent_t e : m->ev_loop) if (e) (void)hipEventDestroy(e);
     for (hipEvent_t e : m->ring) if (e) (void)hipEventDestroy(e);
@@ -580,6 +589,10 @@ emm_status emm_create(const emm_grid *g, const emm_options *o, emm_model **out) 
     // device
     {
         hipError_t e = hipGetDevice(&m->device);
+        int cus = 0, coop = 0;
+        if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, m->device);
+        if (e == hipSuccess) e = hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, m->device);
+        if (e == hipSuccess && coop) m->res = emm::resident_plan(m->r, m->np[0], m->np[1], m->np[2], cus);
         if (e == hipSuccess) e = hipStreamCreate(&m->own_stream);
         // set-up of the static workspace of emm_forward_noalloc on this device
         // (a failure is reported by that call, not here)
@@ -1417,6 +1430,225 @@ emm_status time_loop(emm_model *m, hipStream_t stream, int ckpt) {
     return EMM_OK;
 }
 
+// Whether time loops over nsrc sources of this model run resident
+// (emm_resident.h): the grid has a plan and nothing asks for the
+// launch-per-half-step kernels (their launch options, their timing, the air
+// boundary, the convergence checks).  Resident loops take one source after
+// another; a batch of half-step launches catches up at three sources (us per
+// source and step: 20^3 12.5 alone, 6.7 for two, 4.7 for three, resident 5.3;
+// 48^3 16.7 alone, 11.3 in fives, resident 12.1), at two already where the
+// plan needs more than one plane per thread.
+bool resident_wanted(const emm_model *m, int nsrc) {
+    const emm_options &o = m->opt;
+    return m->res.gy > 0 && nsrc <= (m->res.planes == 1 ? 2 : 1) && !o.airwave && !(o.converge_tol > 0.0) &&
+           !o.profile && !o.fused && o.tile_kz <= 0 && o.tile_x == 0 && o.tile_rows == 0 && o.nontemporal < 0 &&
+           o.src_order < 0 && o.ce_table < 0;
+}
+
+// What a resident run of the prepared acquisition needs beside the state.
+struct ResidentRun {
+    int steps = 0;                       // time steps per launch that the sample buffer holds
+    emm::ResidentParams X{};             // all but the step range, source and snapshots
+};
+
+// false: the run has to go step by step (too many rows with receivers on one
+// tile, no memory).  record: with the receivers' DTFT.
+bool resident_ready(emm_model *m, hipStream_t stream, bool record, ResidentRun &run) {
+    const Acq &A = m->acq;
+    const emm::ResidentPlan &R = m->res;
+    const int L = 2 * m->r, ns = A.nsrc, ny = m->np[1] - L, nz = m->np[2] - L;
+    emm::ResidentParams &X = run.X;
+    // the grid rows under the receivers' stencils (all sources have the same
+    // receivers), the H channels' first, and each item's way to them
+    int per_step = 0;
+    for (int h = 0; h < 2; ++h) {
+        std::vector<emm::ResidentRow> &rows = m->row_h[h];
+        std::vector<int> &way = m->item_rows_h[h];
+        rows.clear();
+        way.clear();
+        const std::vector<int> &items = h ? A.items_hstep : A.items_estep;
+        X.nitems[h] = record ? (int)items.size() / (6 * ns) : 0;
+        if (!X.nitems[h]) continue;
+        std::vector<int> index((size_t)3 * m->np[1] * m->np[2], -1);
+        auto at = [&](const int *inf, int c, int b) -> int & {
+            return index[((size_t)inf[1] * m->np[2] + inf[4] + c) * m->np[1] + inf[3] + b];
+        };
+        for (int q = 0; q < X.nitems[h]; ++q) {
+            const int *inf = &items[(size_t)6 * ns * q];
+            for (int c = 0; c < L; ++c)
+                for (int b = 0; b < L; ++b) {
+                    int &id = at(inf, c, b);
+                    if (id < 0) {
+                        id = (int)rows.size();
+                        rows.push_back({inf[1], inf[3] + b, inf[4] + c, inf[2], L, 0});
+                    } else {
+                        emm::ResidentRow &w = rows[id];
+                        const int end = std::max(w.x0 + w.len, inf[2] + L);
+                        w.x0 = std::min(w.x0, inf[2]);
+                        w.len = end - w.x0;
+                    }
+                }
+        }
+        std::vector<int> load((size_t)R.gy * R.gz, 0);
+        for (emm::ResidentRow &w : rows) {
+            w.off = per_step;
+            per_step += w.len;
+            // tile t along an axis of n cells in g tiles starts at cell n t / g
+            const int by = (int)(((long long)(w.y - m->r) * R.gy + R.gy - 1) / ny),
+                      bz = (int)(((long long)(w.z - m->r) * R.gz + R.gz - 1) / nz);
+            for (int dz = -1; dz <= 0; ++dz)
+                for (int dy = -1; dy <= 0; ++dy) {
+                    const int ty = std::min(std::max(by + dy, 0), R.gy - 1), tz = std::min(std::max(bz + dz, 0), R.gz - 1);
+                    if (w.y - m->r >= ny * ty / R.gy && w.y - m->r < ny * (ty + 1) / R.gy &&
+                        w.z - m->r >= nz * tz / R.gz && w.z - m->r < nz * (tz + 1) / R.gz &&
+                        ++load[tz * R.gy + ty] > emm::kResRows)
+                        return false;
+                }
+        }
+        for (int q = 0; q < X.nitems[h]; ++q) {
+            const int *inf = &items[(size_t)6 * ns * q];
+            for (int c = 0; c < L; ++c)
+                for (int b = 0; b < L; ++b) {
+                    const emm::ResidentRow &w = rows[at(inf, c, b)];
+                    way.push_back(w.off + inf[2] - w.x0);
+                }
+        }
+    }
+    const int nit = X.nitems[0] + X.nitems[1];
+    const size_t mail = (size_t)6 * A.Pe.fstride * sizeof(unsigned long long);
+    if (mail > 0xFFFFFFFFull) return false;              // 32-bit offsets
+    size_t list_bytes = 0, list_at[4] = {};
+    for (int h = 0; h < 2; ++h) {
+        list_at[h] = list_bytes;
+        list_bytes += (m->row_h[h].size() * sizeof(emm::ResidentRow) + 15) / 16 * 16;
+        list_at[2 + h] = list_bytes;
+        list_bytes += (m->item_rows_h[h].size() * sizeof(int) + 15) / 16 * 16;
+    }
+    const size_t step_bytes = (size_t)per_step * sizeof(float) + (size_t)nit * sizeof(double);
+    size_t room = size_t(64) << 20;
+    if (m->arena) {
+        const size_t need = mail + list_bytes + 4096;
+        if (m->arena_used + need + step_bytes > m->arena_cap) return false;
+        room = std::min(room, m->arena_cap - m->arena_used - need);
+    }
+    run.steps = step_bytes ? (int)std::min<size_t>(A.nt, room / step_bytes) : A.nt;
+    if (run.steps < std::min(A.nt, 16)) return false;
+    const size_t old = m->mail.bytes;
+    if (ensure(m, m->mail, mail) != EMM_OK || ensure(m, m->stuck, 256) != EMM_OK ||
+        ensure(m, m->rows, std::max<size_t>(list_bytes, 4)) != EMM_OK ||
+        ensure(m, m->samples, std::max<size_t>(4, (size_t)run.steps * per_step * sizeof(float))) != EMM_OK ||
+        ensure(m, m->sums, std::max<size_t>(4, (size_t)run.steps * nit * sizeof(double))) != EMM_OK) {
+        m->err.clear();
+        return false;
+    }
+    for (int h = 0; h < 2; ++h) {
+        char *d = (char *)m->rows.p;
+        if (!m->row_h[h].empty() &&
+            (hipMemcpyAsync(d + list_at[h], m->row_h[h].data(), m->row_h[h].size() * sizeof(emm::ResidentRow),
+                            hipMemcpyHostToDevice, stream) != hipSuccess ||
+             hipMemcpyAsync(d + list_at[2 + h], m->item_rows_h[h].data(), m->item_rows_h[h].size() * sizeof(int),
+                            hipMemcpyHostToDevice, stream) != hipSuccess))
+            return false;
+        X.rows[h] = (const emm::ResidentRow *)(d + list_at[h]);
+        X.nrows[h] = (int)m->row_h[h].size();
+        X.item_rows[h] = (const int *)(d + list_at[2 + h]);
+    }
+    X.gy = R.gy;
+    X.gz = R.gz;
+    X.ty = R.ty;
+    X.tz = R.tz;
+    X.groups = R.groups;
+    X.mail = (unsigned long long *)m->mail.p;
+    X.samples = (float *)m->samples.p;
+    X.per_step = per_step;
+    X.snap_stride = (long long)3 * ns * A.Pe.fstride;
+    X.stuck = (int *)m->stuck.p;
+    X.patience = 200000000ull;               // 2 s of the 100 MHz wall clock
+    // tags count up over all launches on one mailbox; cleared when it is new,
+    // shared (the static workspace) or the tags would wrap
+    if (m->arena || m->mail.bytes != old || m->mail_tag == 0 || m->mail_tag > 0xF0000000u - 4u * (unsigned)A.nt * ns) {
+        emm::launch_zero(m->mail.p, mail, stream);
+        m->mail_tag = 1;
+    }
+    emm::launch_zero(m->stuck.p, 256, stream);
+    return true;
+}
+
+// Steps [n0, n1) of every source of the prepared acquisition, from the state
+// arrays and back to them.  snap: E after step n also goes to snap slot
+// n - n0.  false: a launch was refused (cooperative queues are one process's
+// at a time on a device); the model goes step by step from then on.
+bool resident_steps(emm_model *m, hipStream_t stream, ResidentRun &run, int n0, int n1, float *snap) {
+    const Acq &A = m->acq;
+    emm::ResidentParams &X = run.X;
+    for (int a = n0; a < n1; a += run.steps)
+        for (int s = 0; s < A.nsrc; ++s) {
+            X.n0 = X.nbase = a;
+            X.n1 = std::min(n1, a + run.steps);
+            X.src = s;
+            X.tag = m->mail_tag + 1;
+            m->mail_tag += 2 * (unsigned)(X.n1 - X.n0) + 2;
+            X.snap = snap ? snap + (long long)(a - n0) * X.snap_stride : nullptr;
+            if (emm::launch_resident(m->r, m->res, A.Pe, A.Ph, X, stream) != hipSuccess) {
+                (void)hipGetLastError();
+                m->res.gy = 0;
+                return false;
+            }
+            if (X.nitems[0] + X.nitems[1] > 0)
+                emm::launch_resident_dft(m->r, A.Pe, A.Ph, X, (double *)m->sums.p, stream);
+        }
+    return true;
+}
+
+// time_loop for a grid that runs resident: the same steps, results,
+// checkpoints and info, one launch per source and stretch of steps.  A wait
+// that ran out of time (it means that the blocks were not all on the chip)
+// sends the run to time_loop.
+emm_status run_loop(emm_model *m, hipStream_t stream, int ckpt) {
+    ResidentRun run;
+    if (!resident_wanted(m, m->acq.nsrc) || !resident_ready(m, stream, true, run)) return time_loop(m, stream, ckpt);
+    Acq &A = m->acq;
+    emm_status st;
+    const int nt = A.nt;
+    if ((st = zero_state(m, stream)) != EMM_OK) return st;
+    if (ckpt > 0) {
+        const int nck = (nt + ckpt - 1) / ckpt;
+        if ((st = ensure(m, m->ckpts, (size_t)nck * state_floats(m) * A.nsrc * sizeof(float))) != EMM_OK) return st;
+    }
+    const bool loop_events = !m->arena;
+    if (loop_events && !m->ev_loop[0]) {
+        HIP_OK(m, hipEventCreate(&m->ev_loop[0]));
+        HIP_OK(m, hipEventCreate(&m->ev_loop[1]));
+    }
+    if (loop_events) HIP_OK(m, hipEventRecord(m->ev_loop[0], stream));
+    for (int n = 0; n < nt; n += ckpt > 0 ? ckpt : nt) {
+        if (ckpt > 0 && (st = copy_state(m, m->ckpts.p, n / ckpt, true, stream)) != EMM_OK) return st;
+        if (!resident_steps(m, stream, run, n, ckpt > 0 ? std::min(nt, n + ckpt) : nt, nullptr))
+            return time_loop(m, stream, ckpt);
+    }
+    HIP_OK(m, hipGetLastError());
+    if (loop_events) HIP_OK(m, hipEventRecord(m->ev_loop[1], stream));
+    int stuck = 0;
+    HIP_OK(m, hipMemcpyAsync(&stuck, m->stuck.p, sizeof(int), hipMemcpyDeviceToHost, stream));
+    HIP_OK(m, hipStreamSynchronize(stream));
+    if (stuck) {
+        m->mail_tag = 0;
+        m->res.gy = 0;
+        return time_loop(m, stream, ckpt);
+    }
+    float loop_ms = 0.f;
+    if (loop_events) HIP_OK(m, hipEventElapsedTime(&loop_ms, m->ev_loop[0], m->ev_loop[1]));
+    A.ckpt = ckpt;
+    m->info.nt = nt;
+    m->info.converged = 0;
+    m->info.forward_ms = loop_ms;
+    note_run(m, A.Pe);
+    m->info.fused = 0;
+    m->info.e_kernel_ms = m->info.h_kernel_ms = 0.0;
+    m->info.e_launches = m->info.h_launches = 0;
+    return EMM_OK;
+}
+
 // Accumulators back to the host (complex, per slot and frequency).
 emm_status read_acc(emm_model *m, hipStream_t stream, std::vector<std::complex<double>> &acc) {
     const Acq &A = m->acq;
@@ -1874,8 +2106,8 @@ emm_status emm_forward(emm_model *m, const emm_source *src, int nsrc, const emm_
         const int ng = std::min(g, nsrc - g0);
         if ((st = prepare(m, src ? src + g0 : src, ng, rec, nrec, chan_mask, freq_hz, nfreq, stream)) != EMM_OK)
             return st;
-        if ((st = autotune(m, stream)) != EMM_OK) return st;
-        if ((st = leap ? leap_loop(m, stream) : time_loop(m, stream, m->opt.checkpoint_every)) != EMM_OK) return st;
+        if (!resident_wanted(m, ng) && (st = autotune(m, stream)) != EMM_OK) return st;
+        if ((st = leap ? leap_loop(m, stream) : run_loop(m, stream, m->opt.checkpoint_every)) != EMM_OK) return st;
         const size_t per_src = (size_t)m->acq.nrec * m->acq.nch * m->acq.nf * 2;
         if ((st = write_green(m, stream, green + (size_t)g0 * per_src)) != EMM_OK) return st;
         fwd_ms += m->info.forward_ms;
@@ -1908,7 +2140,8 @@ emm_status emm_forward_noalloc(emm_model *m, const emm_source *src, int nsrc,
     // the forward-lifetime buffers of earlier emm_forward calls stay aside
     // (and allocated) while this call carves its own from the workspace
     DevBuf *bufs[] = {&m->fields, &m->psi, &m->acc, &m->cpml, &m->srcinfo, &m->srcq,
-                      &m->wav, &m->items, &m->itemw, &m->phase, &m->stepdev};
+                      &m->wav, &m->items, &m->itemw, &m->phase, &m->stepdev,
+                      &m->mail, &m->samples, &m->sums, &m->stuck, &m->rows};
     constexpr int kBufs = sizeof(bufs) / sizeof(bufs[0]);
     DevBuf saved[kBufs];
     for (int b = 0; b < kBufs; ++b) {
@@ -1916,18 +2149,20 @@ emm_status emm_forward_noalloc(emm_model *m, const emm_source *src, int nsrc,
         *bufs[b] = DevBuf{};
     }
     const emm_options opt_saved = m->opt;
+    const unsigned tag_saved = m->mail_tag;
     m->opt.graph_steps = 0;        // direct launches: no graph to instantiate
     m->opt.profile = 0;            // no timing events
     m->arena = (char *)m->scratch;
     m->arena_cap = kScratchBytes;
     m->arena_used = 0;
     emm_status st = prepare(m, src, nsrc, rec, nrec, chan_mask, freq_hz, nfreq, stream);
-    if (st == EMM_OK) st = time_loop(m, stream, 0);
+    if (st == EMM_OK) st = run_loop(m, stream, 0);
     if (st == EMM_OK) st = write_green(m, stream, green);
     if (st != EMM_OK) (void)hipStreamSynchronize(stream);
     m->arena = nullptr;
     m->arena_cap = m->arena_used = 0;
     m->opt = opt_saved;
+    m->mail_tag = tag_saved;
     for (int b = 0; b < kBufs; ++b) *bufs[b] = saved[b];
     m->acq.valid = false;          // its parameters point into the workspace
     m->acq.ckpt = 0;
@@ -2036,6 +2271,7 @@ emm_status gradient_run(emm_model *m, const emm_source *src, int nsrc, const emm
                         const double *g_bar, double *green, double &chi_acc, double *grad, bool accumulate,
                         hipStream_t stream) {
     emm_status st;
+    const double chi_before = chi_acc;
     // forward with checkpoints, unless the last forward stored them for the same acquisition
     const bool reuse = m->acq.ckpt > 0 && same_acquisition(m->acq, src, nsrc, rec, nrec, chan_mask, freq_hz, nfreq);
     if (!reuse) {
@@ -2059,7 +2295,7 @@ emm_status gradient_run(emm_model *m, const emm_source *src, int nsrc, const emm
         m->info.ckpt_inner = std::min(c1, c2);
         m->info.ckpt_bytes = (double)ckpt_memory(A0.nt, c1, c2, S, F);
     }
-    if (!reuse && (st = time_loop(m, stream, c1)) != EMM_OK) return st;
+    if (!reuse && (st = run_loop(m, stream, c1)) != EMM_OK) return st;
     const Acq &A = m->acq;
     const int ckpt = A.ckpt;                 // outer interval
     const int cin = std::min(c2, ckpt);      // inner interval
@@ -2158,9 +2394,9 @@ emm_status gradient_run(emm_model *m, const emm_source *src, int nsrc, const emm
     if ((st = ensure(m, m->adjt, (size_t)std::max<long long>(1, nsrc * slab_src) * sizeof(float))) != EMM_OK) return st;
     // cells off the update set are read as halo and never written: zero in
     // every slot, so cleared when the buffer is new or its slots move
-    const void *snaps_before = m->snaps.p;
+    const size_t snaps_before = m->snaps.bytes;
     if ((st = ensure(m, m->snaps, (size_t)(cin + 1) * 3 * nsrc * fstride * sizeof(float))) != EMM_OK) return st;
-    if (m->snaps.p != snaps_before || m->snaps_nsrc != nsrc) {
+    if (m->snaps.bytes != snaps_before || m->snaps_nsrc != nsrc) {
         HIP_OK(m, hipMemsetAsync(m->snaps.p, 0, m->snaps.bytes, stream));
         m->snaps_nsrc = nsrc;
     }
@@ -2380,6 +2616,8 @@ emm_status gradient_run(emm_model *m, const emm_source *src, int nsrc, const emm
     Pe.nitems = Ph.nitems = 0;
     float *snap = (float *)m->snaps.p;
     const size_t snap_bytes = (size_t)3 * nsrc * fstride * sizeof(float);
+    ResidentRun rerun;
+    bool resident = resident_wanted(m, nsrc) && resident_ready(m, stream, false, rerun);
     // one segment [n0, nend) from checkpoint c of buffer `base`: recompute it
     // with the E step writing out of place into the next snapshot slot (so E
     // after every step is kept without copies), then reverse its steps
@@ -2388,7 +2626,11 @@ emm_status gradient_run(emm_model *m, const emm_source *src, int nsrc, const emm
         if ((s2 = copy_state(m, base, c, false, stream)) != EMM_OK) return s2;
         HIP_OK(m, hipMemcpyAsync(snap, m->fields.p, snap_bytes, hipMemcpyDeviceToDevice, stream));
         const size_t cs = (size_t)nsrc * fstride;               // component stride
-        for (int n = n0; n < nend; ++n) {
+        if (resident && !resident_steps(m, stream, rerun, n0, nend, snap + 3 * cs)) {
+            resident = false;
+            if ((s2 = copy_state(m, base, c, false, stream)) != EMM_OK) return s2;
+        }
+        for (int n = n0; !resident && n < nend; ++n) {
             float *Ein = snap + (size_t)(n - n0) * 3 * cs, *Eout = snap + (size_t)(n - n0 + 1) * 3 * cs;
             emm::StepParams Pr = Pe, Qr = Ph;
             Pr.E1 = Ein;
@@ -2429,6 +2671,11 @@ emm_status gradient_run(emm_model *m, const emm_source *src, int nsrc, const emm
         for (int q = 0; q < nq; ++q) {
             if ((st = copy_state(m, m->ickpts.p, q, true, stream)) != EMM_OK) return st;
             if (q == nq - 1) break;
+            if (resident && resident_steps(m, stream, rerun, n0 + q * cin, n0 + (q + 1) * cin, nullptr)) continue;
+            if (resident) {
+                resident = false;
+                if ((st = copy_state(m, m->ickpts.p, q, false, stream)) != EMM_OK) return st;
+            }
             for (int n = n0 + q * cin; n < n0 + (q + 1) * cin; ++n) {
                 emm::launch_e_step(r, Pe, n, stream);
                 emm::launch_h_step(r, Ph, n, stream);
@@ -2437,6 +2684,19 @@ emm_status gradient_run(emm_model *m, const emm_source *src, int nsrc, const emm
         for (int q = nq - 1; q >= 0; --q)
             if ((st = reverse_segment(m->ickpts.p, q, n0 + q * cin, std::min(n0 + (q + 1) * cin, nend))) != EMM_OK)
                 return st;
+    }
+    if (resident) {
+        int stuck = 0;
+        HIP_OK(m, hipMemcpyAsync(&stuck, m->stuck.p, sizeof(int), hipMemcpyDeviceToHost, stream));
+        HIP_OK(m, hipStreamSynchronize(stream));
+        if (stuck) {                             // as in run_loop: once more, step by step
+            m->mail_tag = 0;
+            m->res.gy = 0;
+            m->acq.ckpt = 0;
+            chi_acc = chi_before;
+            return gradient_run(m, src, nsrc, rec, nrec, chan_mask, freq_hz, nfreq, g_obs, g_bar, green, chi_acc,
+                                grad, accumulate, stream);
+        }
     }
     // sum over sources, drop the pitch padding, fold the model padding back onto
     // the input cells, and change sign: d/d log sigma = -d/d log(dt/eps); on

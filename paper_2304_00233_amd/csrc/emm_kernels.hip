@@ -28,6 +28,7 @@
 // them is loaded once.  Tiles are mapped to the eight XCDs in contiguous
 // ranges so that neighbouring tiles share an L2.
 #include "emm_internal.h"
+#include "emm_rec.h"
 
 #include <hip/hip_ext.h>
 
@@ -81,36 +82,15 @@ __device__ void rec_dft(const StepParams &p, int blk, const float *F0,
     const int s = inf[0], f = inf[1], bx = inf[2], by = inf[3], bz = inf[4], slot = inf[5];
     const float *w = p.item_w + 3 * L * item;
     const float *F = (f == 0 ? F0 : (f == 1 ? F1 : F2)) + (long long)s * p.fstride;
-    double u = 0.0;
-    for (int q = lane; q < L * L * L; q += 64) {
-        const int a = q % L, b = (q / L) % L, c = q / (L * L);
-        const float wt = w[a] * w[L + b] * w[2 * L + c];
-        u += (double)wt * (double)F[(unsigned)((bz + c) * (int)p.plane + (by + b) * p.pitch + bx + a)];
-    }
-    for (int off = 32; off > 0; off >>= 1) u += __shfl_xor(u, off, 64);
+    const double u = rec_sum<R>(w, lane, [&](int, int a, int b, int c) {
+        return F[(unsigned)((bz + c) * (int)p.plane + (by + b) * p.pitch + bx + a)];
+    });
     // lane fr updates frequencies fr, fr + 64, ... (any number of them)
     for (int fr = lane; fr < p.nf; fr += 64) {
         const double2 ph = p.phase[(long long)n * p.nf + fr];
         const long long k = (long long)slot * p.nf + fr;
-        if (p.dft_mode == 0) {
-            double2 a = p.acc[k];
-            a.x += u * ph.x;
-            a.y += u * ph.y;
-            p.acc[k] = a;
-        } else {
-            // FP32 Kahan-compensated sum: (re, c_re, im, c_im)
-            float4 a = p.acck[k];
-            const float uf = (float)u;
-            const float xr = uf * (float)ph.x, xi = uf * (float)ph.y;
-            float y = xr - a.y, t = a.x + y;
-            a.y = (t - a.x) - y;
-            a.x = t;
-            y = xi - a.w;
-            t = a.z + y;
-            a.w = (t - a.z) - y;
-            a.z = t;
-            p.acck[k] = a;
-        }
+        if (p.dft_mode == 0) rec_add(p.acc[k], u, ph);
+        else rec_add(p.acck[k], u, ph);
     }
 }
 

@@ -1,0 +1,69 @@
+// Whole time loops in one launch, for grids whose state fits on the chip.
+#pragma once
+
+#include "emm_internal.h"
+
+#include <vector>
+
+namespace emm {
+
+constexpr int kResPlanes = 5;         // planes per thread at most
+// threads per tile at most: 128 registers each hold one plane, more take 256
+constexpr int resident_threads(int planes) { return planes == 1 ? 1024 : 512; }
+// words a thread receives per half step at most
+constexpr int resident_words(int planes) { return planes == 1 ? 8 : 12; }
+constexpr int kResTall = 32;          // planes per tile at most
+constexpr int kResSlot = 6200;        // floats of one field component's tile in LDS
+constexpr int kResRows = 192;         // sampled rows per tile and half step at most
+
+// The split of a grid's update set into gy x gz tiles of whole x rows, one
+// per compute unit; a tile's planes go to groups of `planes` planes.
+struct ResidentPlan {
+    int gy = 0, gz = 0;               // 0: the grid does not qualify
+    int ty = 0, tz = 0;               // largest tile: rows, planes
+    int planes = 0, groups = 0;       // planes per thread, thread groups
+    int threads = 0;
+};
+
+// Plan for a padded grid, or gy = 0.  cus: compute units of the device.
+ResidentPlan resident_plan(int r, int n1, int n2, int n3, int cus);
+
+// A stretch of one grid row that receiver stencils read: x0 <= i < x0 + len
+// of component comp at (y, z), kept at offset off of a step's samples.
+struct ResidentRow {
+    int comp, y, z, x0, len, off;
+};
+
+struct ResidentParams {
+    int gy, gz, ty, tz, groups;       // as in the plan
+    unsigned long long *mail;         // [6][n3][n2][pitch] words (tag << 32 | value) of tile edges
+    unsigned tag;                     // tag of this launch's first half step; each counts one up
+    int n0, n1;                       // time steps [n0, n1)
+    int src;                          // source
+    // receiver samples [n - nbase][per_step]: rows of H (read in the E step)
+    // and E (in the H step)
+    const ResidentRow *rows[2];
+    int nrows[2];
+    float *samples;
+    int nbase, per_step;
+    // items of one source (item q of the source is item q * nsrc + src of
+    // its list): offset of the samples of stencil row (c, b), [item][(2r)^2]
+    const int *item_rows[2];
+    int nitems[2];
+    float *snap;                      // not null: E after step n also goes to snap + (n - n0) * snap_stride
+    long long snap_stride;
+    int *stuck;                       // set when a wait ran out of time (the run is then void)
+    unsigned long long patience;      // wall-clock ticks a wait may take
+};
+
+// One cooperative launch of steps [n0, n1) for one source: state from pe / ph
+// field and CPML arrays and back to them.
+hipError_t launch_resident(int r, const ResidentPlan &plan, const StepParams &pe, const StepParams &ph,
+                           const ResidentParams &x, hipStream_t s);
+
+// DTFT of the samples of steps [n0, n1): u (double [n - nbase][items]) is
+// scratch.
+void launch_resident_dft(int r, const StepParams &pe, const StepParams &ph, const ResidentParams &x, double *u,
+                         hipStream_t s);
+
+}  // namespace emm
