@@ -58,8 +58,9 @@ struct InjectParams {
     int scale_ce;                 // 0: targets are Hb (unscaled)
 };
 
-void launch_adj_filter(bool rev_h, const AdjParams &p, hipStream_t st);
-void launch_adj_inject(const InjectParams &p, int n, hipStream_t st);
+// the CPML reverse filter (unless !filter) and, in the same launch, the
+// receiver adjoint sources q of step n that precede it (n < 0: none)
+void launch_adj_filter(bool rev_h, const AdjParams &p, bool filter, const InjectParams &q, int n, hipStream_t st);
 void launch_adj_flush(const AdjParams &p, hipStream_t st);
 // the gradient per source and padded cell [s][c][cells] summed over sources
 // and folded onto the input cells (negated: d/dlog sigma = -d/dlog(dt/eps)),

@@ -2643,14 +2643,14 @@ emm_status gradient_run(emm_model *m, const emm_source *src, int nsrc, const emm
             emm::launch_h_step(r, Qr, n, stream);
         }
         for (int n = nend - 1; n >= n0; --n) {
-            if (nb) emm::launch_adj_filter(true, PE, stream);
+            if (n == nend - 1) emm::launch_adj_filter(true, PE, nb > 0, IH, -1, stream);
             emm::launch_adj_tile(r, true, PE, stream);
-            emm::launch_adj_inject(IE, n, stream);
             PH.E_next = snap + (size_t)(n - n0 + 1) * 3 * nsrc * fstride;
             PH.E_prev = snap + (size_t)(n - n0) * 3 * nsrc * fstride;
-            if (nb) emm::launch_adj_filter(false, PH, stream);
+            emm::launch_adj_filter(false, PH, nb > 0, IE, n, stream);
             emm::launch_adj_tile(r, false, PH, stream);
-            emm::launch_adj_inject(IH, n, stream);
+            // this step's H sources with the filter that starts the next
+            emm::launch_adj_filter(true, PE, nb > 0 && n > n0, IH, n, stream);
             // FP32 partial gradient sums cover the steps down to a multiple
             // of kFlush: the same steps under every checkpoint schedule
             if (n % kFlush == 0) emm::launch_adj_flush(PH, stream);

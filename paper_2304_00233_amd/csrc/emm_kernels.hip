@@ -27,6 +27,7 @@
 // components live in a 2r-deep register queue per column, so every plane of
 // them is loaded once.  Tiles are mapped to the eight XCDs in contiguous
 // ranges so that neighbouring tiles share an L2.
+#include "emm_access.h"
 #include "emm_internal.h"
 #include "emm_rec.h"
 
@@ -56,17 +57,6 @@ __device__ __forceinline__ float cpml_mem(float b, float psi, float a, float d) 
     return __builtin_fmaf(b, psi, a * d);
 }
 
-template <bool ST, typename P>
-__device__ __forceinline__ auto ld1(P p) {
-    if constexpr (ST) return __builtin_nontemporal_load(p);
-    else return *p;
-}
-template <bool ST>
-__device__ __forceinline__ void st1(float *p, float v) {
-    if constexpr (ST) __builtin_nontemporal_store(v, p);
-    else *p = v;
-}
-
 // Receiver sample + DTFT: one wavefront per (source, receiver, channel)
 // item.  u = sum over the (2r)^3 tensor-product stencil of w * F, reduced in
 // FP64; then acc[f] += u * exp(i w'_f t_n) for every frequency (lane l takes
@@ -92,31 +82,6 @@ __device__ void rec_dft(const StepParams &p, int blk, const float *F0,
         if (p.dft_mode == 0) rec_add(p.acc[k], u, ph);
         else rec_add(p.acck[k], u, ph);
     }
-}
-
-__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-
-// Global accesses of the plane loop: (scalar 64-bit base of a plane) + (32-bit
-// byte offset of the thread's column), the pair that one load or store
-// instruction takes, so that a plane's accesses cost no vector arithmetic.
-// keep_s / keep_v stop the compiler from folding a sum of scalars into the
-// vector part and from widening a column offset ahead of the loop.
-typedef __attribute__((address_space(1))) char gchar;
-typedef __attribute__((address_space(1))) float gfloat;
-typedef __attribute__((address_space(1))) unsigned guint;
-__device__ __forceinline__ gchar *keep_s(gchar *q) {
-    asm("" : "+s"(q));
-    return q;
-}
-__device__ __forceinline__ void keep_v(unsigned &off) { asm("" : "+v"(off)); }
-template <bool ST>
-__device__ __forceinline__ float ldp(const gchar *pl, unsigned off) {
-    return ld1<ST>((const gfloat *)(pl + off));
-}
-template <bool ST>
-__device__ __forceinline__ void stp(gchar *pl, unsigned off, float v) {
-    if constexpr (ST) __builtin_nontemporal_store(v, (gfloat *)(pl + off));
-    else *(gfloat *)(pl + off) = v;
 }
 
 // ST: nontemporal hints on the updated field and dt/eps.
