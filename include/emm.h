@@ -128,10 +128,10 @@ typedef struct {
                               unless the autotuner (tile_kz = -1) measures the FP32 arrays
                               faster; 1: whenever possible; 0: never [-1] */
     int    src_group;      /* sources per time loop of emm_forward, which runs the loops one after
-                              another (results are the same bit for bit): 0 = as many as keep the
-                              arrays of one step within 160 MiB, so they stay in the 256 MB
-                              Infinity Cache between steps, or all when one source alone does
-                              not fit; -1 = all; k > 0 = k. With checkpoint_every or converge_tol
+                              another (results are the same bit for bit): 0 = as few loops of even
+                              size as keep the arrays of one step within 200 MB, so they stay in
+                              the 256 MB Infinity Cache between steps, or all when one source
+                              alone does not fit; -1 = all; k > 0 = k. With checkpoint_every or converge_tol
                               set, all sources run in one loop. emm_gradient groups its sources
                               too (0 = the most whose checkpoints fit one level, see there) [0] */
     int    tile_x;         /* columns per block of the stencil kernels: 64 (x 4 rows) or 32 (x 8
@@ -283,10 +283,10 @@ typedef struct {
  * device).  Each job's green is exactly what emm_forward writes for it
  * (bitwise).  Jobs run in consecutive groups, group after group, by the
  * src_group option of the first job's model: -1 = all jobs together,
- * k > 0 = k jobs per group, 0 = as many jobs as keep their arrays within
- * 160 MiB (the Infinity Cache rule of emm_forward; a job that alone exceeds
- * it runs by itself), except that a group takes more jobs while its grids
- * hold fewer than 4 Mi cells in all (too few to fill the chip);
+ * k > 0 = k jobs per group, 0 = as few groups of even size as keep their
+ * arrays within 200 MB (the Infinity Cache rule of emm_forward), except that
+ * a group takes more jobs while its grids hold fewer than 2.5 million cells in all
+ * (too few to fill the chip);
  * info.src_group of each model then holds the number of jobs in its group.
  * A model may appear in one job only; every model must live on the same
  * device.  hip_stream: the work starts after what is queued on it and it

@@ -273,6 +273,8 @@ int choose_kz(const emm_model *m, int xt, int yt, int nsrc) {
     // pays: a chunk reloads 2r - 1 planes of two components, yet short chunks
     // keep neighbouring tiles' halos closer in time.  us a step, E + H, one
     // source:  48^3, r = 2: 17.8 at 4, 18.7 at 3, 19.5 at 6, 21.9 at 8
+    //          eight sources there 149 at 4, 157 at 6, 158 at 8 (and 42.6
+    //          against 44.2 on 41 x 174 x 87: r <= 2 with few planes)
     //          20^3: 12.0 at 3, 13.4 at 4;  r = 4: 13.8 and 15.5
     //          90 x 80 x 40, r = 4: 26.6 at 6, 29.2 at 4, 27.7 at 8
     //          128 x 128 x 96, r = 2: 51.8 at 6, 53.2 at 7; r = 4: 67.0 at
@@ -284,8 +286,8 @@ int choose_kz(const emm_model *m, int xt, int yt, int nsrc) {
     //          400 x 400 x 200, r = 4: 804 at 39, 826 at 24 (40 planes
     //          while 4096 blocks remain)
     const long long cols = (long long)xt * yt * nsrc;
-    auto chunks = [&](long long kz) { return std::max<long long>(1, (nzv + kz / 2) / kz); };
-    const int top = m->r <= 3 ? 6 : cols * chunks(40) >= 4096 ? 40 : 24;
+    auto chunks = [&](long long kz) { return (nzv + kz - 1) / kz; };
+    const int top = m->r <= 2 && nzv < 112 ? 4 : m->r <= 3 ? 6 : cols * chunks(40) >= 4096 ? 40 : 24;
     const long long want = std::min<long long>(top, std::max<long long>(3, (cols * nzv + 320) / 640));
     const long long zc = chunks(want);
     return (int)((nzv + zc - 1) / zc);
@@ -779,19 +781,29 @@ size_t state_floats(const emm_model *m) {
     return (size_t)(6 * fstride + 4 * (psxs + psys + pszs));
 }
 
+// Bytes of one source's state, and of dt/eps, that a step moves through the
+// caches: whole 128-byte lines of each row, not the rest of its pitch.
+double touched_bytes(const emm_model *m) {
+    const double row = (m->np[0] + 31) / 32 * 32, n2 = m->np[1], n3 = m->np[2], nb2 = 2.0 * m->nb;
+    return 4.0 * (6.0 * row * n2 * n3 + 4.0 * nb2 * (n2 * n3 + row * n3 + row * n2));
+}
+double touched_model_bytes(const emm_model *m, bool compact) {
+    return (compact ? 4.0 : 12.0) * ((m->np[0] + 31) / 32 * 32) * m->np[1] * m->np[2];
+}
+
 // Sources per time loop of emm_forward: the src_group option, else (0) as
-// many as keep the arrays of one step within 160 MiB, so that they stay in
-// the 256 MB Infinity Cache from step to step (batching sources on such a
-// grid measured slower than one source after another), or all of them when
-// one source alone does not fit.
+// many as keep the lines of one step within 200 MB, so that they stay in the
+// 256 MB Infinity Cache from step to step, in groups of even size (16 on
+// 48^3: 45 ms in eights, 48 in sixes, 51 in fours, 52 in fives and one, 54 all
+// at once), or all of them when one source alone does not fit.
 int source_group(const emm_model *m, int nsrc) {
     if (m->opt.src_group > 0) return std::min(m->opt.src_group, nsrc);
     if (m->opt.src_group < 0) return nsrc;
-    const double budget = 160.0 * (1 << 20);
-    const double per = 4.0 * (double)state_floats(m);
-    const double shared = (double)m->pitch * m->np[1] * m->np[2] * (choose_compact(m, nsrc) ? 4.0 : 12.0);
+    const double budget = 200e6;
+    const double per = touched_bytes(m), shared = touched_model_bytes(m, choose_compact(m, nsrc) != 0);
     if (per + shared > budget) return nsrc;
-    return std::max(1, std::min(nsrc, (int)((budget - shared) / per)));
+    const int most = std::max(1, (int)((budget - shared) / per)), groups = (nsrc + most - 1) / most;
+    return (nsrc + groups - 1) / groups;
 }
 
 emm_status prepare(emm_model *m, const emm_source *src, int nsrc, const emm_receiver *rec, int nrec,
@@ -2199,36 +2211,39 @@ emm_status emm_forward_batch(const emm_job *jobs, int njobs, int graph_steps, vo
             return st;
         if ((st = autotune(J.model, stream)) != EMM_OK) return st;
     }
-    // jobs in consecutive groups, one graph per group, group after group
-    // (src_group of the first job's model: -1 all jobs in one graph, k > 0
-    // k jobs per graph, 0 as many as keep their arrays within the cache
-    // budget of source_group; a job that alone exceeds it runs by itself)
+    // jobs in consecutive groups, group after group (src_group of the first
+    // job's model: -1 all jobs in one group, k > 0 k jobs per group, 0 as few
+    // groups as the cache budget of source_group allows, of even size: eight
+    // models of 98^3 to 136^3 padded cells 22.5 ms in 4 + 2 + 2, 23.9 in 4 +
+    // 3 + 1, 25.3 all at once)
     const int rule = ms[0]->opt.src_group;
-    const double budget = 160.0 * (1 << 20);
-    const double fill = 4.0 * (1 << 20);             // cells that keep the chip busy on their own
+    const double budget = 200e6;
+    const double fill = 2.5e6;                       // cells that keep the chip busy on their own
+    std::vector<double> need(njobs);
+    double total = 0.0;
+    for (int j = 0; j < njobs; ++j) {
+        need[j] = touched_bytes(ms[j]) * jobs[j].nsrc + touched_model_bytes(ms[j], ms[j]->acq.Pe.cei != nullptr);
+        total += need[j];
+    }
+    const double share = total / std::ceil(total / budget);
     std::vector<emm_model *> group;
-    double held = 0.0, cells = 0.0;
+    double before = 0.0, cells = 0.0;                // bytes of the jobs before j, cells of the group
+    int at = 0;                                      // share that the group's last job lies in
     for (int j = 0; j <= njobs; ++j) {
-        double need = 0.0;
-        if (j < njobs) {
-            emm_model *m = ms[j];
-            need = 4.0 * (double)state_floats(m) * jobs[j].nsrc +
-                   (double)m->pitch * m->np[1] * m->np[2] * (m->acq.Pe.cei ? 4.0 : 12.0);
-        }
-        // a group closes when the next job would overflow the cache budget,
-        // unless the group is still too small to fill the chip
-        const bool full = rule < 0 ? false
-                          : rule > 0 ? (int)group.size() == rule
-                                     : held + need > budget && cells >= fill;
+        const int next = j < njobs ? (int)((before + 0.5 * need[j]) / share) : 0;
+        // a group closes at the next share, unless it is still too small to
+        // fill the chip
+        const bool full = rule < 0 ? false : rule > 0 ? (int)group.size() == rule : next > at && cells >= fill;
         if (!group.empty() && (j == njobs || full)) {
             if ((st = time_loop_jobs(group, graph_steps > 0 ? graph_steps : 64, stream)) != EMM_OK) return st;
             for (emm_model *m : group) m->info.src_group = (int)group.size();
             group.clear();
-            held = cells = 0.0;
+            cells = 0.0;
         }
         if (j < njobs) {
             group.push_back(ms[j]);
-            held += need;
+            at = next;
+            before += need[j];
             cells += (double)ms[j]->np[0] * ms[j]->np[1] * ms[j]->np[2] * jobs[j].nsrc;
         }
     }
