@@ -87,6 +87,7 @@ struct Acq {
     std::vector<float> w_estep, w_hstep;
     emm::StepParams Pe{}, Ph{};
     int ckpt = 0;                                   // checkpoint interval of the stored run (0: none)
+    bool snaps_whole = false;                       // the E snapshots hold every step of the stored run
     int nslot = 0;                                  // receiver slots (src, rec, chan)
     int ncorner = 0;                                // convergence-check slots after them (8 per source)
     int fmin_index = 0;                             // lowest frequency
@@ -811,6 +812,7 @@ emm_status prepare(emm_model *m, const emm_source *src, int nsrc, const emm_rece
     Acq &A = m->acq;
     A.valid = false;
     A.ckpt = 0;
+    A.snaps_whole = false;
     if (!src || !rec || nsrc < 1 || nrec < 1 || chan_mask == 0 || (chan_mask & ~0x3Fu))
         return fail(m, EMM_ERR_ARG, "bad sources, receivers or channel mask");
     if (!freq_hz || nfreq < 1) return fail(m, EMM_ERR_FREQ, "need at least one frequency");
@@ -2277,6 +2279,90 @@ emm_status ckpt_budget(emm_model *m, int g, size_t &bud) {
     return EMM_OK;
 }
 
+// Room for `slots` E snapshots of nsrc sources.  Cells off the update set are
+// read as halo and never written: zero in every slot, so cleared when the
+// buffer is new or its slots move.
+emm_status ready_snaps(emm_model *m, int nsrc, size_t slots, hipStream_t stream) {
+    emm_status st;
+    const size_t before = m->snaps.bytes;
+    const size_t slot = (size_t)3 * nsrc * m->pitch * m->np[1] * m->np[2] * sizeof(float);
+    if ((st = ensure(m, m->snaps, slots * slot)) != EMM_OK) return st;
+    if (m->snaps.bytes != before || m->snaps_nsrc != nsrc) {
+        HIP_OK(m, hipMemsetAsync(m->snaps.p, 0, m->snaps.bytes, stream));
+        m->snaps_nsrc = nsrc;
+    }
+    return EMM_OK;
+}
+
+// Parameters of step n's half steps with E going from snapshot slot n - n0 to
+// the next.
+void snap_step(const Acq &A, float *snap, int slot, emm::StepParams &Pe, emm::StepParams &Ph) {
+    const size_t cs = (size_t)A.nsrc * A.Pe.fstride;            // component stride
+    float *in = snap + (size_t)slot * 3 * cs, *out = in + 3 * cs;
+    Pe.E1 = in;
+    Pe.E2 = in + cs;
+    Pe.E3 = in + 2 * cs;
+    Pe.Eo1 = Ph.E1 = Ph.Eo1 = out;
+    Pe.Eo2 = Ph.E2 = Ph.Eo2 = out + cs;
+    Pe.Eo3 = Ph.E3 = Ph.Eo3 = out + 2 * cs;
+}
+
+// The forward of a gradient that keeps E after every step (slot n + 1 of the
+// snapshots): the reverse sweep then recomputes nothing.
+emm_status snapshot_loop(emm_model *m, hipStream_t stream) {
+    Acq &A = m->acq;
+    emm_status st;
+    const int nt = A.nt;
+    float *snap = (float *)m->snaps.p;
+    const size_t slot = (size_t)3 * A.nsrc * A.Pe.fstride;
+    if (!m->ev_loop[0]) {
+        HIP_OK(m, hipEventCreate(&m->ev_loop[0]));
+        HIP_OK(m, hipEventCreate(&m->ev_loop[1]));
+    }
+    ResidentRun run;
+    bool resident = resident_wanted(m, A.nsrc) && resident_ready(m, stream, true, run);
+    for (int attempt = 0; attempt < 2; ++attempt) {
+        if ((st = zero_state(m, stream)) != EMM_OK) return st;
+        HIP_OK(m, hipMemsetAsync(snap, 0, slot * sizeof(float), stream));
+        HIP_OK(m, hipEventRecord(m->ev_loop[0], stream));
+        if (resident) {
+            int stuck = 1;
+            if (resident_steps(m, stream, run, 0, nt, snap + slot)) {
+                HIP_OK(m, hipEventRecord(m->ev_loop[1], stream));
+                HIP_OK(m, hipMemcpyAsync(&stuck, m->stuck.p, sizeof(int), hipMemcpyDeviceToHost, stream));
+                HIP_OK(m, hipStreamSynchronize(stream));
+            }
+            if (!stuck) break;
+            m->mail_tag = 0;
+            m->res.gy = 0;
+            resident = false;
+            continue;
+        }
+        for (int n = 0; n < nt; ++n) {
+            emm::StepParams Pe = A.Pe, Ph = A.Ph;
+            snap_step(A, snap, n, Pe, Ph);
+            emm::launch_e_step(m->r, Pe, n, stream);
+            emm::launch_h_step(m->r, Ph, n, stream);
+        }
+        HIP_OK(m, hipGetLastError());
+        HIP_OK(m, hipEventRecord(m->ev_loop[1], stream));
+        break;
+    }
+    HIP_OK(m, hipStreamSynchronize(stream));
+    float loop_ms = 0.f;
+    HIP_OK(m, hipEventElapsedTime(&loop_ms, m->ev_loop[0], m->ev_loop[1]));
+    A.ckpt = nt;
+    A.snaps_whole = true;
+    m->info.nt = nt;
+    m->info.converged = 0;
+    m->info.forward_ms = loop_ms;
+    note_run(m, A.Pe);
+    m->info.fused = 0;
+    m->info.e_kernel_ms = m->info.h_kernel_ms = 0.0;
+    m->info.e_launches = m->info.h_launches = 0;
+    return EMM_OK;
+}
+
 // One forward + reverse sweep over the sources given (see emm_gradient).
 // accumulate: add dL/dlog sigma onto grad and the misfit onto chi in the
 // order a single call over all sources would (so groups of sources give
@@ -2295,6 +2381,7 @@ emm_status gradient_run(emm_model *m, const emm_source *src, int nsrc, const emm
     }
     // checkpoint schedule within the memory left for it
     int c1 = 0, c2 = 0;
+    bool whole = false;
     {
         const Acq &A0 = m->acq;
         const long long fs = A0.Pe.fstride;
@@ -2302,15 +2389,30 @@ emm_status gradient_run(emm_model *m, const emm_source *src, int nsrc, const emm
         const size_t F = (size_t)3 * A0.nsrc * fs * sizeof(float);
         size_t bud = 0;
         if ((st = ckpt_budget(m, A0.nsrc, bud)) != EMM_OK) return st;
-        if (!plan_checkpoints(A0.nt, m->opt.graph_steps, reuse ? A0.ckpt : m->opt.checkpoint_every,
-                              m->opt.checkpoint_inner, S, F, bud, c1, c2))
+        // a planned run whose E snapshots of every step take an eighth of
+        // that memory at most keeps them all and recomputes nothing (two
+        // shots of 256 steps on 128 x 128 x 96 nodes, 12 GB: 128 ms with a
+        // segment recomputed every 64 steps)
+        whole = reuse ? A0.snaps_whole
+                      : m->opt.checkpoint_every == 0 && m->opt.checkpoint_inner == 0 &&
+                            (size_t)(A0.nt + 1) * F <= bud / 8;
+        if (whole) {
+            c1 = c2 = A0.nt;
+        } else if (!plan_checkpoints(A0.nt, m->opt.graph_steps, reuse ? A0.ckpt : m->opt.checkpoint_every,
+                                     m->opt.checkpoint_inner, S, F, bud, c1, c2)) {
             return fail(m, EMM_ERR_OOM, "no checkpoint schedule fits in " + std::to_string(bud) +
                                             " bytes of device memory; run fewer sources per call");
+        }
         m->info.ckpt_outer = c1;
         m->info.ckpt_inner = std::min(c1, c2);
-        m->info.ckpt_bytes = (double)ckpt_memory(A0.nt, c1, c2, S, F);
+        m->info.ckpt_bytes = whole ? (double)(A0.nt + 1) * F : (double)ckpt_memory(A0.nt, c1, c2, S, F);
     }
-    if (!reuse && (st = run_loop(m, stream, c1)) != EMM_OK) return st;
+    if (!reuse && whole) {
+        if ((st = ready_snaps(m, nsrc, (size_t)m->acq.nt + 1, stream)) != EMM_OK) return st;
+        if ((st = snapshot_loop(m, stream)) != EMM_OK) return st;
+    } else if (!reuse && (st = run_loop(m, stream, c1)) != EMM_OK) {
+        return st;
+    }
     const Acq &A = m->acq;
     const int ckpt = A.ckpt;                 // outer interval
     const int cin = std::min(c2, ckpt);      // inner interval
@@ -2407,14 +2509,7 @@ emm_status gradient_run(emm_model *m, const emm_source *src, int nsrc, const emm
     if ((st = ensure(m, m->adjf, (size_t)6 * nsrc * fstride * sizeof(float))) != EMM_OK) return st;
     if ((st = ensure(m, m->adjq, (size_t)std::max<long long>(1, 2 * nsrc * slab_src) * sizeof(float))) != EMM_OK) return st;
     if ((st = ensure(m, m->adjt, (size_t)std::max<long long>(1, nsrc * slab_src) * sizeof(float))) != EMM_OK) return st;
-    // cells off the update set are read as halo and never written: zero in
-    // every slot, so cleared when the buffer is new or its slots move
-    const size_t snaps_before = m->snaps.bytes;
-    if ((st = ensure(m, m->snaps, (size_t)(cin + 1) * 3 * nsrc * fstride * sizeof(float))) != EMM_OK) return st;
-    if (m->snaps.bytes != snaps_before || m->snaps_nsrc != nsrc) {
-        HIP_OK(m, hipMemsetAsync(m->snaps.p, 0, m->snaps.bytes, stream));
-        m->snaps_nsrc = nsrc;
-    }
+    if ((st = ready_snaps(m, nsrc, (size_t)cin + 1, stream)) != EMM_OK) return st;
     if (cin < ckpt &&
         (st = ensure(m, m->ickpts, (size_t)((ckpt + cin - 1) / cin) * state_floats(m) * nsrc * sizeof(float))) != EMM_OK)
         return st;
@@ -2632,30 +2727,26 @@ emm_status gradient_run(emm_model *m, const emm_source *src, int nsrc, const emm
     float *snap = (float *)m->snaps.p;
     const size_t snap_bytes = (size_t)3 * nsrc * fstride * sizeof(float);
     ResidentRun rerun;
-    bool resident = resident_wanted(m, nsrc) && resident_ready(m, stream, false, rerun);
+    bool resident = !whole && resident_wanted(m, nsrc) && resident_ready(m, stream, false, rerun);
     // one segment [n0, nend) from checkpoint c of buffer `base`: recompute it
     // with the E step writing out of place into the next snapshot slot (so E
     // after every step is kept without copies), then reverse its steps
+    // (nothing to recompute when every step's E is there)
     auto reverse_segment = [&](void *base, int c, int n0, int nend) -> emm_status {
         emm_status s2;
-        if ((s2 = copy_state(m, base, c, false, stream)) != EMM_OK) return s2;
-        HIP_OK(m, hipMemcpyAsync(snap, m->fields.p, snap_bytes, hipMemcpyDeviceToDevice, stream));
-        const size_t cs = (size_t)nsrc * fstride;               // component stride
-        if (resident && !resident_steps(m, stream, rerun, n0, nend, snap + 3 * cs)) {
-            resident = false;
+        if (!whole) {
             if ((s2 = copy_state(m, base, c, false, stream)) != EMM_OK) return s2;
-        }
-        for (int n = n0; !resident && n < nend; ++n) {
-            float *Ein = snap + (size_t)(n - n0) * 3 * cs, *Eout = snap + (size_t)(n - n0 + 1) * 3 * cs;
-            emm::StepParams Pr = Pe, Qr = Ph;
-            Pr.E1 = Ein;
-            Pr.E2 = Ein + cs;
-            Pr.E3 = Ein + 2 * cs;
-            Pr.Eo1 = Qr.E1 = Qr.Eo1 = Eout;
-            Pr.Eo2 = Qr.E2 = Qr.Eo2 = Eout + cs;
-            Pr.Eo3 = Qr.E3 = Qr.Eo3 = Eout + 2 * cs;
-            emm::launch_e_step(r, Pr, n, stream);
-            emm::launch_h_step(r, Qr, n, stream);
+            HIP_OK(m, hipMemcpyAsync(snap, m->fields.p, snap_bytes, hipMemcpyDeviceToDevice, stream));
+            if (resident && !resident_steps(m, stream, rerun, n0, nend, snap + 3 * nsrc * fstride)) {
+                resident = false;
+                if ((s2 = copy_state(m, base, c, false, stream)) != EMM_OK) return s2;
+            }
+            for (int n = n0; !resident && n < nend; ++n) {
+                emm::StepParams Pr = Pe, Qr = Ph;
+                snap_step(A, snap, n - n0, Pr, Qr);
+                emm::launch_e_step(r, Pr, n, stream);
+                emm::launch_h_step(r, Qr, n, stream);
+            }
         }
         for (int n = nend - 1; n >= n0; --n) {
             if (n == nend - 1) emm::launch_adj_filter(true, PE, nb > 0, IH, -1, stream);

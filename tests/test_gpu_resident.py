@@ -48,3 +48,25 @@ def test_gradient_recomputed_resident(emm, rd, every, inner):
     with emm.Model(w, **opt) as m:
         g1, G1, _ = m.gradient(g_bar=np.ones((1, 7, 6, 2), complex))
     assert np.array_equal(G0, G1) and np.array_equal(g0, g1)
+
+
+@pytest.mark.parametrize("rd,nsrc,opt", [(2, 1, {}), (2, 1, dict(src_order=0)), (2, 3, dict(graph_steps=8)),
+                                         (4, 2, {}), (1, 2, {})])
+def test_gradient_with_every_step_kept(emm, rd, nsrc, opt):
+    """Planned intervals keep E of every step when it is small: the same
+    gradient as from checkpoints, also when the next call reuses the run and
+    when another source has used the snapshots in between."""
+    w = configs.small_case(seed=50 + rd, shape=(22, 21, 20), rd=rd, nb=5, ne=rd + 2, nt=53, nsrc=nsrc)
+    bar = np.ones((nsrc, 7, 6, 2), complex)
+    print(f"[gpu] gradient, every step kept r{rd} nsrc{nsrc} {opt}", flush=True)
+    with emm.Model(w, checkpoint_every=20, **opt) as m:
+        g0, G0, _ = m.gradient(g_bar=bar)
+    with emm.Model(w, **opt) as m:
+        g1, G1, _ = m.gradient(g_bar=bar)
+        i = m.info()
+        assert i["ckpt_outer"] == i["ckpt_inner"] == 53 and i["ckpt_bytes"] > 0
+        g2, G2, _ = m.gradient(g_bar=bar)
+        m.gradient(g_bar=bar[:1], sources=w.sources[:1])
+        g3, G3, _ = m.gradient(g_bar=bar)
+    for g, G in ((g1, G1), (g2, G2), (g3, G3)):
+        assert np.array_equal(G0, G) and np.array_equal(g0, g)
