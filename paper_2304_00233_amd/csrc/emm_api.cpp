@@ -621,17 +621,18 @@ emm_status emm_create(const emm_grid *g, const emm_options *o, emm_model **out) 
     std::vector<float> ctab;
     std::unordered_map<uint32_t, unsigned> code;
     if (opt.ce_table != 0) cidx.assign(N, 0u);
+    const int p0 = m->np[0], p1 = m->np[1], p2 = m->np[2], pitch = m->pitch, nbe = m->nbe, n0 = nd[0];
+    const double per_rho = m->dt * 2.0 * m->omega0;
     for (int c3 = 0; c3 < 3; ++c3) {
-        for (int k = 0; k < m->np[2]; ++k) {
-            const int kk = std::min(std::max(k - m->nbe, 0), nd[2] - 1);
-            for (int j = 0; j < m->np[1]; ++j) {
-                const int jj = std::min(std::max(j - m->nbe, 0), nd[1] - 1);
-                float *row = &buf[((long long)k * m->np[1] + j) * m->pitch];
-                const float *src = rho[c3] + ((long long)kk * nd[1] + jj) * nd[0];
-                for (int i = 0; i < m->np[0]; ++i) {
-                    const int ii = std::min(std::max(i - m->nbe, 0), nd[0] - 1);
-                    row[i] = (float)(m->dt * 2.0 * m->omega0 * (double)src[ii]);
-                }
+        for (int k = 0; k < p2; ++k) {
+            const int kk = std::min(std::max(k - nbe, 0), nd[2] - 1);
+            for (int j = 0; j < p1; ++j) {
+                const int jj = std::min(std::max(j - nbe, 0), nd[1] - 1);
+                float *row = &buf[((long long)k * p1 + j) * pitch];
+                const float *src = rho[c3] + ((long long)kk * nd[1] + jj) * n0;
+                for (int i = 0; i < n0; ++i) row[nbe + i] = (float)(per_rho * (double)src[i]);
+                for (int i = 0; i < nbe; ++i) row[i] = row[nbe];
+                for (int i = nbe + n0; i < p0; ++i) row[i] = row[nbe + n0 - 1];
             }
         }
         if (!cidx.empty()) {
@@ -639,12 +640,16 @@ emm_status emm_create(const emm_grid *g, const emm_options *o, emm_model **out) 
             uint32_t last_bits = 0;
             unsigned last = 0;
             bool have_last = false;
-            for (int k = 0; k < m->np[2] && !cidx.empty(); ++k)
-                for (int j = 0; j < m->np[1] && !cidx.empty(); ++j) {
-                    const long long row = ((long long)k * m->np[1] + j) * m->pitch;
-                    for (int i = 0; i < m->np[0]; ++i) {
+            // (the padding repeats interior values: codes appear in the order
+            // of the interior scan)
+            for (int k = 0; k < p2 && !cidx.empty(); ++k)
+                for (int j = 0; j < p1 && !cidx.empty(); ++j) {
+                    const long long row = ((long long)k * p1 + j) * pitch;
+                    const float *value = &buf[row];
+                    unsigned *index = &cidx[row];
+                    for (int i = 0; i < p0; ++i) {
                         uint32_t bits;
-                        std::memcpy(&bits, &buf[row + i], 4);
+                        std::memcpy(&bits, &value[i], 4);
                         if (!have_last || bits != last_bits) {
                             auto it = code.find(bits);
                             if (it == code.end()) {
@@ -652,14 +657,14 @@ emm_status emm_create(const emm_grid *g, const emm_options *o, emm_model **out) 
                                     cidx.clear();    // too many values: FP32 arrays
                                     break;
                                 }
-                                ctab.push_back(buf[row + i]);
+                                ctab.push_back(value[i]);
                                 it = code.emplace(bits, (unsigned)code.size()).first;
                             }
                             last_bits = bits;
-                            last = it->second;
+                            last = it->second << (8 * c3);
                             have_last = true;
                         }
-                        cidx[row + i] |= last << (8 * c3);
+                        index[i] |= last;
                     }
                 }
         }
