@@ -45,14 +45,12 @@ TRAFFIC_KIB = {
     # (workload, kernel, tx, ry, source order, nontemporal, compact, nsrc, kz):
     #     (FETCH_SIZE KiB, WRITE_SIZE KiB); the large grid at 8th order with 8
     #     sources (profiles/step_kernel_large_marine_*)
-    ("large_marine_400x400x200", "e_step", 32, 1, 1, 0, 1, 8, 58): (6401647.6, 4453677.2),
-    ("large_marine_400x400x200", "h_step", 32, 1, 1, 0, 1, 8, 58): (5792745.6, 4453299.9),
-    ("large_marine_400x400x200", "e_step", 64, 1, 1, 0, 1, 8, 58): (6574432.7, 4450545.0),
-    ("large_marine_400x400x200", "h_step", 64, 1, 1, 0, 1, 8, 58): (5874936.8, 4454413.7),
-    ("large_marine_400x400x200", "e_step", 32, 1, 1, 1, 1, 8, 58): (5845896.3, 4449371.8),
-    ("large_marine_400x400x200", "h_step", 32, 1, 1, 1, 1, 8, 58): (5187237.2, 4451036.2),
-    ("large_marine_400x400x200", "e_step", 64, 1, 1, 1, 1, 8, 58): (5762863.4, 4433150.8),
-    ("large_marine_400x400x200", "h_step", 64, 1, 1, 1, 1, 8, 58): (5067565.9, 4436068.8),
+    ("large_marine_400x400x200", "e_step", 64, 1, 1, 0, 1, 8, 39): (6611073.0, 4452997.0),
+    ("large_marine_400x400x200", "h_step", 64, 1, 1, 0, 1, 8, 39): (5802557.5, 4452042.0),
+    ("large_marine_400x400x200", "e_step", 64, 1, 1, 0, 1, 8, 46): (6890961.1, 4455365.2),
+    ("large_marine_400x400x200", "h_step", 64, 1, 1, 0, 1, 8, 46): (6042486.9, 4455570.9),
+    ("large_marine_400x400x200", "e_step", 64, 1, 1, 0, 1, 8, 58): (7247091.6, 4456257.9),
+    ("large_marine_400x400x200", "h_step", 64, 1, 1, 0, 1, 8, 58): (6376854.2, 4457145.1),
 }
 FETCH_SCALE, WRITE_SCALE = 2.0, 1.0
 
