@@ -2,31 +2,11 @@
 #pragma once
 
 #include "emm_internal.h"
+#include "emm_resident_plan.h"
 
 #include <vector>
 
 namespace emm {
-
-constexpr int kResPlanes = 5;         // planes per thread at most
-// threads per tile at most: 128 registers each hold one plane, more take 256
-constexpr int resident_threads(int planes) { return planes == 1 ? 1024 : 512; }
-// words a thread receives per half step at most
-constexpr int resident_words(int planes) { return planes == 1 ? 8 : 12; }
-constexpr int kResTall = 32;          // planes per tile at most
-constexpr int kResSlot = 6200;        // floats of one field component's tile in LDS
-constexpr int kResRows = 192;         // sampled rows per tile and half step at most
-
-// The split of a grid's update set into gy x gz tiles of whole x rows, one
-// per compute unit; a tile's planes go to groups of `planes` planes.
-struct ResidentPlan {
-    int gy = 0, gz = 0;               // 0: the grid does not qualify
-    int ty = 0, tz = 0;               // largest tile: rows, planes
-    int planes = 0, groups = 0;       // planes per thread, thread groups
-    int threads = 0;
-};
-
-// Plan for a padded grid, or gy = 0.  cus: compute units of the device.
-ResidentPlan resident_plan(int r, int n1, int n2, int n3, int cus);
 
 // A stretch of one grid row that receiver stencils read: x0 <= i < x0 + len
 // of component comp at (y, z), kept at offset off of a step's samples.
