@@ -76,18 +76,21 @@ typedef struct {
     double cpml_alpha_max; /* frequency-shift maximum; 0 = pi * f_peak [0] */
     double wavelet_fpeak;  /* source wavelet peak frequency; 0 = 2 sqrt(f_max f0) [0] */
     int    allow_unstable; /* test hook: accept dt_override above the CFL limit [0] */
-    int    profile;        /* 1 = time stencil launches with HIP events that the dispatch
+    int    profile;        /* 1 = run half-step launches (never a resident loop, see emm_forward)
+                              and time stencil launches with HIP events that the dispatch
                               stamps at kernel start and end (hipExtLaunchKernel): one E/H pair
                               in 16 direct steps; with graph_steps, every 8th block of steps runs
                               as direct launches and one pair in 4 of them is timed (emm_query) [0] */
     int    tile_kz;        /* z planes per thread block; 0 = chosen from the grid, -1 = autotuned
                               together with the nontemporal hint on the first forward (timing
-                              candidates on this model) [0] */
+                              candidates on this model) whose time loop uses the launches (not a
+                              resident loop, see emm_forward) [0] */
     int    checkpoint_every; /* > 0: emm_forward keeps full-state checkpoints every this many
                               steps for a following emm_gradient, and emm_gradient uses this
                               outer interval; 0: emm_gradient plans it (see below) [0] */
     int    graph_steps;    /* > 0: capture this many time steps in one hipGraph and replay it
-                              (a device step counter advances between replays) [0] */
+                              (a device step counter advances between replays); no effect on a
+                              resident loop (see emm_forward) [0] */
     int    checkpoint_inner; /* > 0 and < the outer interval: emm_gradient re-runs each outer
                               segment once to lay inner checkpoints this many steps apart
                               (two levels); 0: planned [0] */
@@ -189,6 +192,10 @@ typedef struct {
     int    src_order;        /* tile order of the sources in the last forward's launches */
     int    air_transform;    /* ghost-fill transforms of the last forward: 0 = no air boundary,
                                 1 = hipFFT, 2 = direct kernels */
+    int    resident;         /* > 0: the last time loop ran resident (see emm_forward), with this
+                                many z planes per thread; the launch shapes and bytes above are then
+                                those of the half-step launches it stood in for (a gradient's
+                                reverse sweep takes the shapes); 0: launches as above */
 } emm_info;
 
 /* Fill *o with the defaults above: the paper's values where it states them
@@ -227,6 +234,16 @@ emm_status emm_query(const emm_model *m, emm_info *info);
  * channels.  green must hold 2*nsrc*nrec*popcount(chan_mask)*nfreq doubles;
  * nsrc >= 1 and nrec >= 1 (else ARG), any number nfreq >= 1 of frequencies
  * (Section 3.5: one DTFT each; else FREQ).
+ * Small grids (order 2r <= 6, whose state fits in the registers and LDS of
+ * the chip: up to some 80^3 padded cells at r = 2) run resident: the time
+ * steps of one source are one cooperative launch, source after source.  That
+ * is for loops of one source, or two where a thread holds one plane, and
+ * without airwave, converge_tol, profile, fused and any launch option (tile_kz
+ * > 0, tile_x, tile_rows, nontemporal, src_order, ce_table) set: setting one,
+ * to any value but its default, selects the half-step launches.  The results
+ * are the same bit for bit.  A resident loop whose launch is refused, or whose
+ * blocks wait for each other for more than 2 s, is run again as half-step
+ * launches, which the model then keeps to.  info.resident tells which ran.
  * hip_stream: a hipStream_t to run on, or NULL for the library's own stream.
  * Errors: ARG, GEOMETRY, FREQ, NONFINITE, OOM, DEVICE. */
 emm_status emm_forward(emm_model *m, const emm_source *src, int nsrc,
@@ -241,9 +258,10 @@ emm_status emm_forward(emm_model *m, const emm_source *src, int nsrc,
  * all live in one static device workspace of 128 MiB per device (held from
  * the library's first use on a device until the process ends); it calls no
  * hipMalloc / hipFree, creates no event or graph, and clears what must start
- * at zero with a fill kernel.  It runs every source in one time loop of
- * direct launches (graph_steps and profile are ignored for the call; tiles:
- * the model's option or earlier autotuned choice, no autotuning).  A call
+ * at zero with a fill kernel.  It runs every source in one time loop,
+ * resident where emm_forward's would be (graph_steps and profile are ignored
+ * for the call) and the workspace has room, else direct launches (tiles: the
+ * model's option or earlier autotuned choice, no autotuning).  A call
  * whose buffers exceed 128 MiB fails with EMM_ERR_OOM and a message giving
  * the bytes it needs (about 30 MB per source on a 48^3 grid with 10 CPML
  * layers); the air boundary and checkpoints (options airwave,

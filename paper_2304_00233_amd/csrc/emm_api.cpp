@@ -378,8 +378,10 @@ void set_tiles(emm::StepParams &P, const emm_model *m, int tx, int ry = 1) {
     P.yt = (m->np[1] - 2 * m->r + rows - 1) / rows;
 }
 
-// launch choices of the last run, and the E step's bytes that follow from them
-void note_run(emm_model *m, const emm::StepParams &Pe) {
+// launch choices of the last run, and the E step's bytes that follow from
+// them; resident: planes per thread of a resident loop (0: those launches ran)
+void note_run(emm_model *m, const emm::StepParams &Pe, int resident = 0) {
+    m->info.resident = resident;
     m->info.tile_kz = Pe.kz;
     m->info.tile_x = Pe.tx;
     m->info.tile_rows = Pe.ry;
@@ -1661,7 +1663,7 @@ emm_status run_loop(emm_model *m, hipStream_t stream, int ckpt) {
     m->info.nt = nt;
     m->info.converged = 0;
     m->info.forward_ms = loop_ms;
-    note_run(m, A.Pe);
+    note_run(m, A.Pe, m->res.planes);
     m->info.fused = 0;
     m->info.e_kernel_ms = m->info.h_kernel_ms = 0.0;
     m->info.e_launches = m->info.h_launches = 0;
@@ -2361,7 +2363,7 @@ emm_status snapshot_loop(emm_model *m, hipStream_t stream) {
     m->info.nt = nt;
     m->info.converged = 0;
     m->info.forward_ms = loop_ms;
-    note_run(m, A.Pe);
+    note_run(m, A.Pe, resident ? m->res.planes : 0);
     m->info.fused = 0;
     m->info.e_kernel_ms = m->info.h_kernel_ms = 0.0;
     m->info.e_launches = m->info.h_launches = 0;

@@ -21,12 +21,36 @@ def test_every_plan_equals_half_step_launches(emm, shape, rd, nb, ne, planes, se
     print(f"[gpu] resident {shape} r{rd} planes {planes} several groups {several}", flush=True)
     with emm.Model(w, src_order=0) as m:
         ref = m.forward()
+        assert m.info()["resident"] == 0
     with emm.Model(w) as m:
-        assert np.array_equal(m.forward(), ref)
+        assert np.array_equal(m.forward(), ref) and m.info()["resident"] == planes
+        assert np.array_equal(m.forward(noalloc=True), ref) and m.info()["resident"] == planes
     opt = dict(checkpoint_every=16)                # recomputed, E of every step to the snapshots
     bar = np.ones((1, 7, 6, 2), complex)
     with emm.Model(w, src_order=0, **opt) as m:
         g0, _, _ = m.gradient(g_bar=bar)
     with emm.Model(w, **opt) as m:
         g1, _, _ = m.gradient(g_bar=bar)
+        assert m.info()["resident"] == planes
     assert np.array_equal(g0, g1)
+
+
+def test_which_loops_run_resident(emm):
+    """One plane per thread: one and two sources; more: one source; every
+    option that is set selects the half-step launches."""
+    w = configs.small_case(seed=3, shape=(24, 22, 20), nt=20, nsrc=3)
+    two = dict(sources=w.sources[:2], src_comp=w.src_comp[:2])
+    one = dict(sources=w.sources[:1], src_comp=w.src_comp[:1])
+    with emm.Model(w) as m:
+        for kw, planes in ((one, 1), (two, 1), ({}, 0), (one, 1)):
+            m.forward(**kw)
+            assert m.info()["resident"] == planes
+        emm.forward_models([m])
+        assert m.info()["resident"] == 0
+        m.gradient(g_bar=np.ones((1, 7, 6, 2), complex), **one)        # E of every step kept
+        assert m.info()["resident"] == 1
+    for opt in (dict(tile_kz=4), dict(tile_x=64), dict(tile_rows=1), dict(nontemporal=0), dict(ce_table=0),
+                dict(src_order=0), dict(profile=1), dict(fused=1), dict(converge_tol=1e-9)):
+        with emm.Model(w, **opt) as m:
+            m.forward(**one)
+            assert m.info()["resident"] == 0, opt
