@@ -155,6 +155,7 @@ struct emm_model {
     // grid does not qualify), mailbox, receiver samples, their sums, and a
     // flag that a wait ran out of time
     emm::ResidentPlan res;
+    emm::ResidentLimits res_limits;
     DevBuf mail, samples, sums, stuck, rows;
     std::vector<emm::ResidentRow> row_h[2];         // host copies of what `rows` holds
     std::vector<int> item_rows_h[2];
@@ -1584,7 +1585,7 @@ bool resident_ready(emm_model *m, hipStream_t stream, bool record, ResidentRun &
     X.per_step = per_step;
     X.snap_stride = (long long)3 * ns * A.Pe.fstride;
     X.stuck = (int *)m->stuck.p;
-    X.patience = 200000000ull;               // 2 s of the 100 MHz wall clock
+    X.patience = m->res_limits.patience;
     // tags count up over all launches on one mailbox; cleared when it is new,
     // shared (the static workspace) or the tags would wrap
     if (m->arena || m->mail.bytes != old || m->mail_tag == 0 || m->mail_tag > 0xF0000000u - 4u * (unsigned)A.nt * ns) {
@@ -1610,7 +1611,9 @@ bool resident_steps(emm_model *m, hipStream_t stream, ResidentRun &run, int n0, 
             X.tag = m->mail_tag + 1;
             m->mail_tag += 2 * (unsigned)(X.n1 - X.n0) + 2;
             X.snap = snap ? snap + (long long)(a - n0) * X.snap_stride : nullptr;
-            if (emm::launch_resident(m->r, m->res, A.Pe, A.Ph, X, stream) != hipSuccess) {
+            const bool granted = m->res_limits.launches != 0;
+            if (m->res_limits.launches > 0) --m->res_limits.launches;
+            if (!granted || emm::launch_resident(m->r, m->res, A.Pe, A.Ph, X, stream) != hipSuccess) {
                 (void)hipGetLastError();
                 m->res.gy = 0;
                 return false;
@@ -2102,6 +2105,15 @@ emm_status autotune(emm_model *m, hipStream_t stream) {
 }  // namespace
 
 extern "C" {
+
+// Not part of emm.h: the limits of this model's resident runs, for tests of
+// what follows when a wait runs out (patience 0) or a launch is refused.
+emm_status emm_test_resident(emm_model *m, double patience_s, int launches) {
+    if (!m || !(patience_s >= 0.0)) return fail(m, EMM_ERR_ARG, "bad resident limits");
+    m->res_limits.patience = (unsigned long long)(patience_s * 1e8);
+    m->res_limits.launches = launches;
+    return EMM_OK;
+}
 
 emm_status emm_forward(emm_model *m, const emm_source *src, int nsrc, const emm_receiver *rec,
                        int nrec, unsigned chan_mask, const double *freq_hz, int nfreq,

@@ -14,6 +14,13 @@ struct ResidentRow {
     int comp, y, z, x0, len, off;
 };
 
+// What a model grants its resident runs; tests tighten it (emm_test_resident)
+// to send a run the way back to half-step launches.
+struct ResidentLimits {
+    unsigned long long patience = 200000000ull;   // a wait: ticks of the 100 MHz wall clock
+    int launches = -1;                            // cooperative launches (-1: any number)
+};
+
 struct ResidentParams {
     int gy, gz, ty, tz, groups;       // as in the plan
     unsigned long long *mail;         // [6][n3][n2][pitch] words (tag << 32 | value) of tile edges

@@ -277,6 +277,9 @@ __global__ __launch_bounds__(resident_threads(P)) void resident_kernel(const Ste
                 if (wfrom[A][q] != ~0u) sA[wto[A][q]] = __uint_as_float((unsigned)got[q]);
         }
         __syncthreads();
+        // (a wave behind may see the flag of one that gave up a half step ahead
+        // and leave before it: a barrier waits for the surviving waves only,
+        // and wave 0 sees the flag at the latest at the barrier that follows)
         if (s_stuck) return false;
 
         // ---- compute, post the tile's edges (without branches up to there:
