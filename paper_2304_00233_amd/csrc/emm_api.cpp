@@ -2746,7 +2746,8 @@ emm_status gradient_run(emm_model *m, const emm_source *src, int nsrc, const emm
     float *snap = (float *)m->snaps.p;
     const size_t snap_bytes = (size_t)3 * nsrc * fstride * sizeof(float);
     ResidentRun rerun;
-    bool resident = !whole && resident_wanted(m, nsrc) && resident_ready(m, stream, false, rerun);
+    const bool begun = !whole && resident_wanted(m, nsrc) && resident_ready(m, stream, false, rerun);
+    bool resident = begun;                       // until a launch is refused
     // one segment [n0, nend) from checkpoint c of buffer `base`: recompute it
     // with the E step writing out of place into the next snapshot slot (so E
     // after every step is kept without copies), then reverse its steps
@@ -2810,7 +2811,7 @@ emm_status gradient_run(emm_model *m, const emm_source *src, int nsrc, const emm
             if ((st = reverse_segment(m->ickpts.p, q, n0 + q * cin, std::min(n0 + (q + 1) * cin, nend))) != EMM_OK)
                 return st;
     }
-    if (resident) {
+    if (begun) {                                 // also what ran before a refusal may have given up
         int stuck = 0;
         HIP_OK(m, hipMemcpyAsync(&stuck, m->stuck.p, sizeof(int), hipMemcpyDeviceToHost, stream));
         HIP_OK(m, hipStreamSynchronize(stream));

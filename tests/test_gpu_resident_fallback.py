@@ -72,3 +72,15 @@ def test_gradient_recompute(emm, w, ref, patience, launches, every, inner):
         _limit(emm, m, patience, launches)
         g, G, _ = m.gradient(g_bar=BAR)
         assert np.array_equal(G, ref[0]) and np.array_equal(g, ref[1])
+
+
+@pytest.mark.parametrize("every,inner", [(16, 0), (30, 7)])
+def test_gradient_gives_up_then_is_refused(emm, w, ref, every, inner):
+    """The first recomputed stretch runs out of patience, the next launch is
+    refused: what the first left behind does not count."""
+    print(f"[gpu] recompute gives up, then refused, every {every} inner {inner}", flush=True)
+    with emm.Model(w, checkpoint_every=every, checkpoint_inner=inner) as m:
+        assert np.array_equal(m.forward(), ref[0]) and m.info()["resident"] > 0
+        _limit(emm, m, 0.0, 1)
+        g, G, _ = m.gradient(g_bar=BAR)
+        assert np.array_equal(G, ref[0]) and np.array_equal(g, ref[1])
