@@ -440,13 +440,12 @@ __global__ __launch_bounds__(AT) void adj_flush(const AdjParams p) {
 // grad[s][c][k][j][i], in a fixed order: one block per output row, each thread
 // summing its padded column over the sources, k and j that fold onto the row
 // (up to 15^2 of them at the edges, coalesced in x), then the ends of the row
-// in x.  One thread per output cell did 15^3 uncoalesced sums in a row: 674
+// in x, whose columns alone pass through LDS, so that a row may have any length.  One thread per output cell did 15^3 uncoalesced sums in a row: 674
 // us per gradient on 128 x 128 x 96 nodes.
 __global__ __launch_bounds__(AT) void adj_fold(const double *grad, double *out, int nsrc, long long fstride,
                                                long long plane, int pitch, int n1, int n2, int n3, int r, int nbe,
                                                int nd0, int nd1, int nd2, int accumulate) {
-    extern __shared__ double row[];           // [n1] padded row, then [nd0] output row
-    double *sum = row + n1;
+    extern __shared__ double ends[];          // sums of the padded columns that fold onto the row's two ends
     int b = blockIdx.x;
     const int jj = b % nd1;
     b /= nd1;
@@ -454,34 +453,37 @@ __global__ __launch_bounds__(AT) void adj_fold(const double *grad, double *out, 
     const int j0 = jj == 0 ? r : jj + nbe, j1 = jj == nd1 - 1 ? n2 - 1 - r : jj + nbe;
     const int k0 = kk == 0 ? r : kk + nbe, k1 = kk == nd2 - 1 ? n3 - 1 - r : kk + nbe;
     const int nj = j1 - j0 + 1, rows = nj * (k1 - k0 + 1);
+    const int side = nbe - r + 1;             // columns r .. nbe fold onto the first cell, as many onto the last
     double *o = out + (((long long)c * nd2 + kk) * nd1 + jj) * nd0;
-    for (int ii = threadIdx.x; ii < nd0; ii += AT) sum[ii] = accumulate ? o[ii] : 0.0;
     for (int s = 0; s < nsrc; ++s) {          // one source's fold after another, whatever the grouping
+        const bool add = s > 0 || accumulate;
         for (int i = r + threadIdx.x; i <= n1 - 1 - r; i += AT) {
             const double *g = grad + ((long long)s * 3 + c) * fstride + i;
             double acc = 0.0;
 #pragma unroll 8
             for (int q = 0; q < rows; ++q) acc += g[(long long)(k0 + q / nj) * plane + (long long)(j0 + q % nj) * pitch];
-            row[i] = acc;
+            const int ii = i - nbe;
+            if (ii <= 0) ends[i - r] = acc;
+            else if (ii >= nd0 - 1) ends[side + ii - (nd0 - 1)] = acc;
+            else o[ii] = (add ? o[ii] : 0.0) - acc;
         }
         __syncthreads();
-        for (int ii = threadIdx.x; ii < nd0; ii += AT) {
-            const int i0 = ii == 0 ? r : ii + nbe, i1 = ii == nd0 - 1 ? n1 - 1 - r : ii + nbe;
+        if (threadIdx.x < 2) {
+            const int ii = threadIdx.x ? nd0 - 1 : 0;
             double acc = 0.0;
-            for (int i = i0; i <= i1; ++i) acc += row[i];
-            sum[ii] -= acc;
+            for (int i = 0; i < side; ++i) acc += ends[threadIdx.x * side + i];
+            o[ii] = (add ? o[ii] : 0.0) - acc;
         }
         __syncthreads();
     }
-    for (int ii = threadIdx.x; ii < nd0; ii += AT) o[ii] = sum[ii];
 }
 
 void launch_adj_fold(const double *grad, double *out, int nsrc, long long fstride, long long plane, int pitch,
                      int n1, int n2, int n3, int r, int nbe, int nd0, int nd1, int nd2, bool accumulate,
                      hipStream_t st) {
     const dim3 grid((unsigned)(3 * nd1 * nd2)), block(AT);
-    hipLaunchKernelGGL(adj_fold, grid, block, (n1 + nd0) * sizeof(double), st, grad, out, nsrc, fstride, plane, pitch, n1, n2, n3, r, nbe, nd0,
-                       nd1, nd2, accumulate ? 1 : 0);
+    hipLaunchKernelGGL(adj_fold, grid, block, 2 * (nbe - r + 1) * sizeof(double), st, grad, out, nsrc, fstride, plane,
+                       pitch, n1, n2, n3, r, nbe, nd0, nd1, nd2, accumulate ? 1 : 0);
 }
 
 void launch_adj_flush(const AdjParams &p, hipStream_t st) {
