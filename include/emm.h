@@ -301,10 +301,12 @@ typedef struct {
  * device).  Each job's green is exactly what emm_forward writes for it
  * (bitwise).  Jobs run in consecutive groups, group after group, by the
  * src_group option of the first job's model: -1 = all jobs together,
- * k > 0 = k jobs per group, 0 = as few groups of even size as keep their
- * arrays within 200 MB (the Infinity Cache rule of emm_forward), except that
- * a group takes more jobs while its grids hold fewer than 2.5 million cells in all
- * (too few to fill the chip);
+ * k > 0 = k jobs per group, 0 = as few groups, of even size where that does,
+ * as keep the arrays a step touches within 240 MB (in the 256 MB Infinity
+ * Cache; a job beyond that runs by itself), except that a group takes more
+ * jobs while its grids hold fewer than 2.5 million cells in all (too few to
+ * fill the chip), and that two jobs of one or two sources go together up to
+ * 560 MB;
  * info.src_group of each model then holds the number of jobs in its group.
  * A model may appear in one job only; every model must live on the same
  * device.  hip_stream: the work starts after what is queued on it and it

@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "emm_adjoint.h"
+#include "emm_groups.h"
 #include "emm_internal.h"
 #include "emm_resident.h"
 #include "emm_setup.h"
@@ -2233,40 +2234,30 @@ emm_status emm_forward_batch(const emm_job *jobs, int njobs, int graph_steps, vo
         if ((st = autotune(J.model, stream)) != EMM_OK) return st;
     }
     // jobs in consecutive groups, group after group (src_group of the first
-    // job's model: -1 all jobs in one group, k > 0 k jobs per group, 0 as few
-    // groups as the cache budget of source_group allows, of even size: eight
-    // models of 98^3 to 136^3 padded cells 22.5 ms in 4 + 2 + 2, 23.9 in 4 +
-    // 3 + 1, 25.3 all at once)
+    // job's model: -1 all jobs in one group, k > 0 k jobs per group, 0 by the
+    // cache, see batch_groups)
     const int rule = ms[0]->opt.src_group;
-    const double budget = 200e6;
-    const double fill = 2.5e6;                       // cells that keep the chip busy on their own
-    std::vector<double> need(njobs);
-    double total = 0.0;
-    for (int j = 0; j < njobs; ++j) {
-        need[j] = touched_bytes(ms[j]) * jobs[j].nsrc + touched_model_bytes(ms[j], ms[j]->acq.Pe.cei != nullptr);
-        total += need[j];
+    std::vector<int> sizes;
+    if (rule == 0) {
+        std::vector<double> need(njobs), cells(njobs);
+        std::vector<int> nsrc(njobs);
+        for (int j = 0; j < njobs; ++j) {
+            const emm_model *m = ms[j];
+            need[j] = touched_bytes(m) * jobs[j].nsrc + touched_model_bytes(m, m->acq.Pe.cei != nullptr);
+            cells[j] = (double)m->np[0] * m->np[1] * m->np[2] * jobs[j].nsrc;
+            nsrc[j] = jobs[j].nsrc;
+        }
+        sizes = emm::batch_groups(need, cells, nsrc);
+    } else {
+        const int k = rule > 0 ? rule : njobs;
+        for (int j = 0; j < njobs; j += k) sizes.push_back(std::min(k, njobs - j));
     }
-    const double share = total / std::ceil(total / budget);
-    std::vector<emm_model *> group;
-    double before = 0.0, cells = 0.0;                // bytes of the jobs before j, cells of the group
-    int at = 0;                                      // share that the group's last job lies in
-    for (int j = 0; j <= njobs; ++j) {
-        const int next = j < njobs ? (int)((before + 0.5 * need[j]) / share) : 0;
-        // a group closes at the next share, unless it is still too small to
-        // fill the chip
-        const bool full = rule < 0 ? false : rule > 0 ? (int)group.size() == rule : next > at && cells >= fill;
-        if (!group.empty() && (j == njobs || full)) {
-            if ((st = time_loop_jobs(group, graph_steps > 0 ? graph_steps : 64, stream)) != EMM_OK) return st;
-            for (emm_model *m : group) m->info.src_group = (int)group.size();
-            group.clear();
-            cells = 0.0;
-        }
-        if (j < njobs) {
-            group.push_back(ms[j]);
-            at = next;
-            before += need[j];
-            cells += (double)ms[j]->np[0] * ms[j]->np[1] * ms[j]->np[2] * jobs[j].nsrc;
-        }
+    auto first = ms.begin();
+    for (int size : sizes) {
+        const std::vector<emm_model *> group(first, first + size);
+        first += size;
+        if ((st = time_loop_jobs(group, graph_steps > 0 ? graph_steps : 64, stream)) != EMM_OK) return st;
+        for (emm_model *m : group) m->info.src_group = size;
     }
     for (int j = 0; j < njobs; ++j)
         if ((st = write_green(jobs[j].model, stream, jobs[j].green)) != EMM_OK) return st;
