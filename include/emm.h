@@ -132,7 +132,7 @@ typedef struct {
                               faster; 1: whenever possible; 0: never [-1] */
     int    src_group;      /* sources per time loop of emm_forward, which runs the loops one after
                               another (results are the same bit for bit): 0 = as few loops of even
-                              size as keep the arrays of one step within 200 MB, so they stay in
+                              size as keep the arrays of one step within 240 MB, so they stay in
                               the 256 MB Infinity Cache between steps, or all when one source
                               alone does not fit; -1 = all; k > 0 = k. With checkpoint_every or converge_tol
                               set, all sources run in one loop. emm_gradient groups its sources

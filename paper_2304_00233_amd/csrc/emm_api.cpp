@@ -801,19 +801,12 @@ double touched_model_bytes(const emm_model *m, bool compact) {
     return (compact ? 4.0 : 12.0) * ((m->np[0] + 31) / 32 * 32) * m->np[1] * m->np[2];
 }
 
-// Sources per time loop of emm_forward: the src_group option, else (0) as
-// many as keep the lines of one step within 200 MB, so that they stay in the
-// 256 MB Infinity Cache from step to step, in groups of even size (16 on
-// 48^3: 45 ms in eights, 48 in sixes, 51 in fours, 52 in fives and one, 54 all
-// at once), or all of them when one source alone does not fit.
+// Sources per time loop of emm_forward: the src_group option, else (0) by the
+// cache (see emm::source_group).
 int source_group(const emm_model *m, int nsrc) {
     if (m->opt.src_group > 0) return std::min(m->opt.src_group, nsrc);
     if (m->opt.src_group < 0) return nsrc;
-    const double budget = 200e6;
-    const double per = touched_bytes(m), shared = touched_model_bytes(m, choose_compact(m, nsrc) != 0);
-    if (per + shared > budget) return nsrc;
-    const int most = std::max(1, (int)((budget - shared) / per)), groups = (nsrc + most - 1) / most;
-    return (nsrc + groups - 1) / groups;
+    return emm::source_group(touched_bytes(m), touched_model_bytes(m, choose_compact(m, nsrc) != 0), nsrc);
 }
 
 emm_status prepare(emm_model *m, const emm_source *src, int nsrc, const emm_receiver *rec, int nrec,

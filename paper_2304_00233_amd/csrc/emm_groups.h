@@ -1,11 +1,31 @@
-// Which jobs of a batch run side by side.  Plain C++: its test uses it without
-// HIP.
+// Which sources of a forward, and which jobs of a batch, run side by side.
+// Plain C++: its tests use it without HIP.
 #pragma once
 
-#include <cmath>
+#include <algorithm>
 #include <vector>
 
 namespace emm {
+
+// Bytes a step may touch for several sources of one model to share the 256 MB
+// Infinity Cache.  ms a forward of 100 steps, in groups of the size named:
+//   48^3 nodes, 9 sources (23 MB each)     8.6 in 9 (207 MB), 9.1 in 8, 9.5 in 5
+//   48^3, 16 sources                       15.6 in 8 (184 MB), 16.7 in 10 (229), 18.4 in 16 (365)
+//   37 x 29 x 23, 16 (13 MB)               9.1 in 16 (211 MB), 10.0 in 8
+//   80 x 64 x 50, 12 (35 MB)               17.0 in 6 (214 MB), 18.7 in 4, 20.1 in 8 (285)
+//   64^3, 8 (41 MB)                        11.8 in 4 (167 MB), 13.3 in 8 (332)
+//   90^3, smooth, 6 (62 + 24 MB)           18.4 in 3 (211 MB), 20.2 in 2, 22.3 in 5 (335)
+//   140 x 130 x 130, smooth, 4 (153 + 62)  36.9 in 1 (215 MB), 39.4 in 4
+constexpr double kSourceBudget = 240e6;
+
+// Sources per time loop: as few loops of even size as keep the bytes of a step
+// (per a source and shared by all) within the budget, or all of them in one
+// when one source alone does not fit.
+inline int source_group(double per, double shared, int nsrc) {
+    if (per + shared > kSourceBudget) return nsrc;
+    const int most = std::max(1, (int)((kSourceBudget - shared) / per)), groups = (nsrc + most - 1) / most;
+    return (nsrc + groups - 1) / groups;
+}
 
 // Bytes a step may touch for jobs to share the 256 MB Infinity Cache, and cells
 // that fill the chip (below them more jobs are never worse).  ms for 6 equal

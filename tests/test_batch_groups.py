@@ -1,6 +1,7 @@
-"""Grouping of a batch's jobs on the host: consecutive groups that cover every
+"""Grouping on the host.  A batch's jobs: consecutive groups that cover every
 job, none beyond the cache budget once its jobs fill the chip, except for two
-jobs of one or two sources."""
+jobs of one or two sources.  A forward's sources: loops of even size within
+the budget."""
 import os
 import subprocess
 
@@ -14,6 +15,10 @@ PROGRAM = r"""
 #include <cstdio>
 #include <cstdlib>
 int main(int argc, char **argv) {
+    if (argc == 4) {
+        printf("%d ", emm::source_group(1e6 * atof(argv[1]), 1e6 * atof(argv[2]), atoi(argv[3])));
+        return 0;
+    }
     std::vector<double> need, cells;
     std::vector<int> nsrc;
     for (int a = 1; a + 2 < argc; a += 3) {
@@ -32,8 +37,8 @@ def groups(tmp_path_factory):
     (d / "g.cpp").write_text(PROGRAM)
     subprocess.run(["g++", "-O1", "-std=c++17", "-I", CSRC, str(d / "g.cpp"), "-o", str(d / "g")], check=True)
 
-    def call(jobs):
-        args = [str(v) for job in jobs for v in job]
+    def call(jobs, source=False):
+        args = [str(v) for job in jobs for v in job] + ([] if source else ["end"])
         return [int(v) for v in subprocess.run([str(d / "g"), *args], capture_output=True, text=True,
                                                check=True).stdout.split()]
     return call
@@ -70,3 +75,11 @@ def test_batch_groups(groups, jobs, want):
         assert (held <= BUDGET or size == 1 or sum(c for _, c, _ in part[:-1]) < FILL or
                 (size == 2 and held <= PAIR and max(s for _, _, s in part) <= 2))
     assert j == len(jobs)
+
+
+# MB of a source, MB shared by all, sources -> sources per loop
+@pytest.mark.parametrize("per,shared,nsrc,want", [(23, 3, 9, 9), (23, 3, 10, 10), (23, 3, 11, 6), (23, 3, 16, 8),
+                                                  (35, 4, 12, 6), (62, 24, 6, 3), (153, 62, 4, 1), (200, 60, 4, 4),
+                                                  (239, 1, 3, 1), (5, 1, 1, 1)])
+def test_source_groups(groups, per, shared, nsrc, want):
+    assert groups([(per, shared, nsrc)], source=True) == [want]
