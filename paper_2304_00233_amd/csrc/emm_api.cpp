@@ -275,19 +275,26 @@ int choose_kz(const emm_model *m, int xt, int yt, int nsrc) {
     // About 640 blocks (2.5 per CU), but 3 planes at least and not more than
     // pays: a chunk reloads 2r - 1 planes of two components, yet short chunks
     // keep neighbouring tiles' halos closer in time.  us a step, E + H, one
-    // source:  48^3, r = 2: 17.8 at 4, 18.7 at 3, 19.5 at 6, 21.9 at 8
-    //          eight sources there 149 at 4, 157 at 6, 158 at 8 (and 42.6
-    //          against 44.2 on 41 x 174 x 87: r <= 2 with few planes)
-    //          20^3: 12.0 at 3, 13.4 at 4;  r = 4: 13.8 and 15.5
-    //          90 x 80 x 40, r = 4: 26.6 at 6, 29.2 at 4, 27.7 at 8
-    //          128 x 128 x 96, r = 2: 51.8 at 6, 53.2 at 7; r = 4: 67.0 at
-    //          11 and 24, 69.7 at 8; r = 3: 61.6 at 6, 62.9 at 8 and 24
-    //          41 x 174 x 87, r = 3: 45.4 at 6, 48.4 at 16; r = 2: 42.6 at
-    //          4, 44.2 at 6
-    //          256^3, r = 2: 402 at 6, 411 at 10, 431 at 22
-    //          200 x 200 x 100, r = 4, two sources: 289 at 22, 297 at 33
-    //          400 x 400 x 200, r = 4: 804 at 39, 826 at 24 (40 planes
-    //          while 4096 blocks remain)
+    // source:
+    //   r <= 2, fewer than 112 update planes, at 4 and 6:
+    //     48^3 17.8 and 19.5 (18.7 at 3, 21.9 at 8), eight sources 149 and 157
+    //     64^3 22.2 and 23.4;  64 x 64 x 80 22.4 and 23.9
+    //     128 x 128 x 60 41.8 and 44.6;  300 x 60 x 80 57.1 and 58.1
+    //   r <= 2, more planes, at 4 and 6:
+    //     90^3 36.8 and 35.8;  200 x 200 x 100 128.5 and 126.0
+    //     128 x 128 x 96 53.9 and 53.4;  256^3 415 and 402
+    //   There, between 4 and 7, a grid may go up to 6 % the other way: the
+    //   number of blocks decides how they fall on the chip (128 x 128 x 96 51.5
+    //   at 5, 256^3 413; 41 x 174 x 87 41.1 at 4, 41.7 at 5, 44.3 at 6; 64 x 64
+    //   x 200 38.6, 39.2, 41.6).  5 for all of them gains and loses as much;
+    //   tile_kz = -1 measures.
+    //   20^3: r = 2 12.0 at 3, 13.4 at 4;  r = 4 13.8 and 15.5
+    //   r = 3: 128 x 128 x 96 61.6 at 6, 62.9 at 8 and 24;  41 x 174 x 87 45.4
+    //     at 6, 48.4 at 16
+    //   r = 4: 90 x 80 x 40 26.6 at 6, 29.2 at 4, 27.7 at 8;  128 x 128 x 96
+    //     67.0 at 11 and 24, 69.7 at 8;  200 x 200 x 100, two sources 289 at
+    //     22, 297 at 33;  400 x 400 x 200 804 at 39, 826 at 24 (40 planes
+    //     while 4096 blocks remain)
     const long long cols = (long long)xt * yt * nsrc;
     auto chunks = [&](long long kz) { return (nzv + kz - 1) / kz; };
     const int top = m->r <= 2 && nzv < 112 ? 4 : m->r <= 3 ? 6 : cols * chunks(40) >= 4096 ? 40 : 24;
