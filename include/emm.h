@@ -84,7 +84,8 @@ typedef struct {
     int    tile_kz;        /* z planes per thread block; 0 = chosen from the grid, -1 = autotuned
                               together with the nontemporal hint on the first forward (timing
                               candidates on this model) whose time loop uses the launches (not a
-                              resident loop, see emm_forward) [0] */
+                              resident loop, see emm_forward, unless it keeps checkpoints: a
+                              gradient's reverse sweep takes the launch shapes) [0] */
     int    checkpoint_every; /* > 0: emm_forward keeps full-state checkpoints every this many
                               steps for a following emm_gradient, and emm_gradient uses this
                               outer interval; 0: emm_gradient plans it (see below) [0] */

@@ -1562,6 +1562,7 @@ bool resident_ready(emm_model *m, hipStream_t stream, bool record, ResidentRun &
         ensure(m, m->samples, std::max<size_t>(4, (size_t)run.steps * per_step * sizeof(float))) != EMM_OK ||
         ensure(m, m->sums, std::max<size_t>(4, (size_t)run.steps * nit * sizeof(double))) != EMM_OK) {
         m->err.clear();
+        (void)hipGetLastError();             // or the half-step launches would report it
         return false;
     }
     for (int h = 0; h < 2; ++h) {
@@ -1625,13 +1626,22 @@ bool resident_steps(emm_model *m, hipStream_t stream, ResidentRun &run, int n0, 
     return true;
 }
 
-// time_loop for a grid that runs resident: the same steps, results,
-// checkpoints and info, one launch per source and stretch of steps.  A wait
+// The launch-per-half-step loop, with the launches autotuned first where the
+// model asks for it (a no-alloc call creates no events, so it takes what an
+// earlier call chose).
+emm_status launch_loop(emm_model *m, hipStream_t stream, int ckpt) {
+    emm_status st;
+    if (!m->arena && (st = autotune(m, stream)) != EMM_OK) return st;
+    return time_loop(m, stream, ckpt);
+}
+
+// launch_loop, or for a grid that runs resident the same steps, results,
+// checkpoints and info in one launch per source and stretch of steps.  A wait
 // that ran out of time (it means that the blocks were not all on the chip)
-// sends the run to time_loop.
+// sends the run to launch_loop.
 emm_status run_loop(emm_model *m, hipStream_t stream, int ckpt) {
     ResidentRun run;
-    if (!resident_wanted(m, m->acq.nsrc) || !resident_ready(m, stream, true, run)) return time_loop(m, stream, ckpt);
+    if (!resident_wanted(m, m->acq.nsrc) || !resident_ready(m, stream, true, run)) return launch_loop(m, stream, ckpt);
     Acq &A = m->acq;
     emm_status st;
     const int nt = A.nt;
@@ -1649,7 +1659,7 @@ emm_status run_loop(emm_model *m, hipStream_t stream, int ckpt) {
     for (int n = 0; n < nt; n += ckpt > 0 ? ckpt : nt) {
         if (ckpt > 0 && (st = copy_state(m, m->ckpts.p, n / ckpt, true, stream)) != EMM_OK) return st;
         if (!resident_steps(m, stream, run, n, ckpt > 0 ? std::min(nt, n + ckpt) : nt, nullptr))
-            return time_loop(m, stream, ckpt);
+            return launch_loop(m, stream, ckpt);
     }
     HIP_OK(m, hipGetLastError());
     if (loop_events) HIP_OK(m, hipEventRecord(m->ev_loop[1], stream));
@@ -1659,7 +1669,7 @@ emm_status run_loop(emm_model *m, hipStream_t stream, int ckpt) {
     if (stuck) {
         m->mail_tag = 0;
         m->res.gy = 0;
-        return time_loop(m, stream, ckpt);
+        return launch_loop(m, stream, ckpt);
     }
     float loop_ms = 0.f;
     if (loop_events) HIP_OK(m, hipEventElapsedTime(&loop_ms, m->ev_loop[0], m->ev_loop[1]));
@@ -2116,6 +2126,9 @@ emm_status emm_test_resident(emm_model *m, double patience_s, int launches) {
     return EMM_OK;
 }
 
+// Source counts whose launches are autotuned.
+int emm_test_tuned(const emm_model *m) { return m ? (int)m->tuned.size() : 0; }
+
 emm_status emm_forward(emm_model *m, const emm_source *src, int nsrc, const emm_receiver *rec,
                        int nrec, unsigned chan_mask, const double *freq_hz, int nfreq,
                        double *green, void *hip_stream) {
@@ -2140,7 +2153,9 @@ emm_status emm_forward(emm_model *m, const emm_source *src, int nsrc, const emm_
         const int ng = std::min(g, nsrc - g0);
         if ((st = prepare(m, src ? src + g0 : src, ng, rec, nrec, chan_mask, freq_hz, nfreq, stream)) != EMM_OK)
             return st;
-        if (!resident_wanted(m, ng) && (st = autotune(m, stream)) != EMM_OK) return st;
+        // (a following gradient's reverse sweep takes the launch shapes of a
+        // checkpointed forward, however that ran)
+        if ((leap || m->opt.checkpoint_every > 0) && (st = autotune(m, stream)) != EMM_OK) return st;
         if ((st = leap ? leap_loop(m, stream) : run_loop(m, stream, m->opt.checkpoint_every)) != EMM_OK) return st;
         const size_t per_src = (size_t)m->acq.nrec * m->acq.nch * m->acq.nf * 2;
         if ((st = write_green(m, stream, green + (size_t)g0 * per_src)) != EMM_OK) return st;

@@ -15,6 +15,7 @@ pytestmark = pytest.mark.gpu
 def emm():
     from paper_2304_00233_amd import emm as m
     m._lib.emm_test_resident.argtypes = [C.c_void_p, C.c_double, C.c_int]
+    m._lib.emm_test_tuned.argtypes = [C.c_void_p]
     return m
 
 
@@ -84,3 +85,21 @@ def test_gradient_gives_up_then_is_refused(emm, w, ref, every, inner):
         _limit(emm, m, 0.0, 1)
         g, G, _ = m.gradient(g_bar=BAR)
         assert np.array_equal(G, ref[0]) and np.array_equal(g, ref[1])
+
+
+def test_autotuned_where_the_launches_run(emm, w, ref):
+    """tile_kz = -1 measures the launches when a time loop uses them: not
+    before a resident loop, but after its refusal, and for a checkpointed
+    forward, whose launch shapes the gradient's reverse sweep takes."""
+    print("[gpu] autotuning beside resident loops", flush=True)
+    with emm.Model(w, tile_kz=-1) as m:
+        assert np.array_equal(m.forward(), ref[0]) and m.info()["resident"] > 0
+        assert emm._lib.emm_test_tuned(m.h) == 0
+        _limit(emm, m, 2.0, 0)
+        assert np.array_equal(m.forward(), ref[0]) and m.info()["resident"] == 0
+        assert emm._lib.emm_test_tuned(m.h) == 1
+        assert np.array_equal(m.forward(), ref[0]) and emm._lib.emm_test_tuned(m.h) == 1
+    with emm.Model(w, tile_kz=-1, checkpoint_every=20) as m:
+        assert np.array_equal(m.forward(), ref[0]) and m.info()["resident"] > 0
+        assert emm._lib.emm_test_tuned(m.h) == 1
+        assert np.array_equal(m.gradient(g_bar=BAR)[0], ref[1])
