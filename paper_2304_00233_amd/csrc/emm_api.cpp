@@ -1264,6 +1264,19 @@ emm_status ensure_events(emm_model *m, size_t count) {
     return EMM_OK;
 }
 
+constexpr int kProfileEvery = 16;   // direct steps per timed one (profile = 1)
+
+// Durations (ms) of the E and H launches that carried the events of a slot.
+emm_status pair_times(emm_model *m, int slot, double &ems, double &hms) {
+    float a = 0.f, b = 0.f;
+    HIP_OK(m, hipEventSynchronize(m->ring[4 * slot + 3]));
+    HIP_OK(m, hipEventElapsedTime(&a, m->ring[4 * slot + 0], m->ring[4 * slot + 1]));
+    HIP_OK(m, hipEventElapsedTime(&b, m->ring[4 * slot + 2], m->ring[4 * slot + 3]));
+    ems += a;
+    hms += b;
+    return EMM_OK;
+}
+
 // Zero the state and run all time steps: per step the E step (+ H-channel
 // DTFT) then the H step (+ E-channel DTFT).  ckpt > 0 stores the full state
 // before every step n with n % ckpt == 0.
@@ -1283,7 +1296,7 @@ emm_status time_loop(emm_model *m, hipStream_t stream, int ckpt) {
     // directly instead -- the same kernels with the absolute step index --
     // and sampled, so the timing is taken inside the timed loop.
     const bool prof = m->opt.profile != 0;
-    const int sample = 16;
+    const int sample = kProfileEvery;
     if (prof) {
         // every timed E/H pair of this forward gets its own four events: no
         // event is recorded twice before the end of the loop reads it
@@ -1298,18 +1311,7 @@ emm_status time_loop(emm_model *m, hipStream_t stream, int ckpt) {
         HIP_OK(m, hipEventCreate(&m->ev_loop[1]));
     }
     double ems = 0.0, hms = 0.0;
-    long long nsamp = 0;
     int nslots_used = 0;
-    auto harvest = [&](int slot) -> emm_status {
-        float a = 0.f, b = 0.f;
-        HIP_OK(m, hipEventSynchronize(m->ring[4 * slot + 3]));
-        HIP_OK(m, hipEventElapsedTime(&a, m->ring[4 * slot + 0], m->ring[4 * slot + 1]));
-        HIP_OK(m, hipEventElapsedTime(&b, m->ring[4 * slot + 2], m->ring[4 * slot + 3]));
-        ems += a;
-        hms += b;
-        ++nsamp;
-        return EMM_OK;
-    };
     // one direct step, bracketed by events when `timed`
     auto step = [&](int n, bool timed) -> emm_status {
         int slot = -1;
@@ -1436,7 +1438,7 @@ emm_status time_loop(emm_model *m, hipStream_t stream, int ckpt) {
     if (loop_events) HIP_OK(m, hipEventRecord(m->ev_loop[1], stream));
     if (prof)
         for (int u = 0; u < nslots_used; ++u)
-            if ((st = harvest(u)) != EMM_OK) return st;
+            if ((st = pair_times(m, u, ems, hms)) != EMM_OK) return st;
     HIP_OK(m, hipStreamSynchronize(stream));
     float loop_ms = 0.f;
     if (loop_events) HIP_OK(m, hipEventElapsedTime(&loop_ms, m->ev_loop[0], m->ev_loop[1]));
@@ -1448,8 +1450,7 @@ emm_status time_loop(emm_model *m, hipStream_t stream, int ckpt) {
     m->info.fused = 0;
     m->info.e_kernel_ms = prof ? ems : 0.0;
     m->info.h_kernel_ms = prof ? hms : 0.0;
-    m->info.e_launches = prof ? nsamp : 0;
-    m->info.h_launches = prof ? nsamp : 0;
+    m->info.e_launches = m->info.h_launches = nslots_used;
     return EMM_OK;
 }
 
@@ -2344,6 +2345,10 @@ emm_status snapshot_loop(emm_model *m, hipStream_t stream) {
         HIP_OK(m, hipEventCreate(&m->ev_loop[0]));
         HIP_OK(m, hipEventCreate(&m->ev_loop[1]));
     }
+    // one step in kProfileEvery timed, as in time_loop (a profiled model never
+    // runs resident)
+    const int timed = m->opt.profile ? (nt + kProfileEvery - 1) / kProfileEvery : 0;
+    if ((st = ensure_events(m, (size_t)4 * timed)) != EMM_OK) return st;
     ResidentRun run;
     bool resident = resident_wanted(m, A.nsrc) && resident_ready(m, stream, true, run);
     for (int attempt = 0; attempt < 2; ++attempt) {
@@ -2366,8 +2371,9 @@ emm_status snapshot_loop(emm_model *m, hipStream_t stream) {
         for (int n = 0; n < nt; ++n) {
             emm::StepParams Pe = A.Pe, Ph = A.Ph;
             snap_step(A, snap, n, Pe, Ph);
-            emm::launch_e_step(m->r, Pe, n, stream);
-            emm::launch_h_step(m->r, Ph, n, stream);
+            hipEvent_t *ev = timed && n % kProfileEvery == 0 ? &m->ring[4 * (n / kProfileEvery)] : nullptr;
+            emm::launch_e_step(m->r, Pe, n, stream, ev ? ev[0] : nullptr, ev ? ev[1] : nullptr);
+            emm::launch_h_step(m->r, Ph, n, stream, ev ? ev[2] : nullptr, ev ? ev[3] : nullptr);
         }
         HIP_OK(m, hipGetLastError());
         HIP_OK(m, hipEventRecord(m->ev_loop[1], stream));
@@ -2384,7 +2390,9 @@ emm_status snapshot_loop(emm_model *m, hipStream_t stream) {
     note_run(m, A.Pe, resident ? m->res.planes : 0);
     m->info.fused = 0;
     m->info.e_kernel_ms = m->info.h_kernel_ms = 0.0;
-    m->info.e_launches = m->info.h_launches = 0;
+    m->info.e_launches = m->info.h_launches = timed;
+    for (int u = 0; u < timed; ++u)
+        if ((st = pair_times(m, u, m->info.e_kernel_ms, m->info.h_kernel_ms)) != EMM_OK) return st;
     return EMM_OK;
 }
 

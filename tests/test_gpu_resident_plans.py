@@ -54,3 +54,19 @@ def test_which_loops_run_resident(emm):
         with emm.Model(w, **opt) as m:
             m.forward(**one)
             assert m.info()["resident"] == 0, opt
+
+
+def test_profiled_gradient_with_every_step_kept(emm):
+    """profile = 1 times the stencil launches of a gradient's forward also when
+    that keeps E of every step."""
+    w = configs.small_case(seed=4, shape=(24, 22, 20), nt=53)
+    bar = np.ones((1, 7, 6, 2), complex)
+    with emm.Model(w) as m:
+        ref, _, _ = m.gradient(g_bar=bar)
+    for opt in ({}, dict(checkpoint_every=20)):
+        with emm.Model(w, profile=1, **opt) as m:
+            g, _, _ = m.gradient(g_bar=bar)
+            i = m.info()
+        assert np.array_equal(g, ref) and i["resident"] == 0
+        assert i["e_launches"] == i["h_launches"] == 4
+        assert 0 < i["e_kernel_ms"] < i["forward_ms"] and 0 < i["h_kernel_ms"] < i["forward_ms"]
