@@ -328,7 +328,10 @@ emm_status emm_forward_batch(const emm_job *jobs, int njobs, int graph_steps, vo
  *   two levels (inner C2 < outer C1): ceil(nt/C1) S + ceil(C1/C2) S + (C2+1) F
  * at the price of one more forward pass.  Intervals left at 0 are planned:
  * when (nt + 1) F takes no more than an eighth of the free device memory, E
- * is kept for every step and nothing is recomputed (both intervals nt);
+ * is kept for every step and nothing is recomputed (both intervals nt; by
+ * direct launches whatever graph_steps; the memory, like that of checkpoints,
+ * is held for further calls until emm_destroy; setting either interval avoids
+ * it);
  * else the one-level interval of least memory if it fits in the free device
  * memory (after the adjoint's own arrays), else the two-level pair of least
  * memory; EMM_ERR_OOM if neither fits (run fewer sources per call).  The

@@ -134,6 +134,7 @@ struct emm_model {
     // gradients, transposed tables, injection lists and coefficients
     DevBuf adjf, adjq, adjt, snaps, grad, grad32, tabT, inj, injA, adjcpml;
     int snaps_nsrc = 0;                             // sources the cleared E snapshots are laid out for
+    double snap_share = 0.125;                      // of the memory left, for E of every step
     DevBuf gsum;                                    // dL/dlog sigma on the input cells, summed over sources
     // receiver injection lists of the last emm_gradient (CSR over target
     // cells, in m->inj), kept while the acquisition's receiver items, the
@@ -2127,6 +2128,14 @@ emm_status emm_test_resident(emm_model *m, double patience_s, int launches) {
     return EMM_OK;
 }
 
+// Share of the memory left that E of every step may take in a gradient (0: the
+// intervals are planned).
+emm_status emm_test_snapshots(emm_model *m, double share) {
+    if (!m || !(share >= 0.0)) return fail(m, EMM_ERR_ARG, "bad snapshot share");
+    m->snap_share = share;
+    return EMM_OK;
+}
+
 // Source counts whose launches are autotuned.
 int emm_test_tuned(const emm_model *m) { return m ? (int)m->tuned.size() : 0; }
 
@@ -2428,7 +2437,7 @@ emm_status gradient_run(emm_model *m, const emm_source *src, int nsrc, const emm
         // segment recomputed every 64 steps)
         whole = reuse ? A0.snaps_whole
                       : m->opt.checkpoint_every == 0 && m->opt.checkpoint_inner == 0 &&
-                            (size_t)(A0.nt + 1) * F <= bud / 8;
+                            (double)(A0.nt + 1) * F <= m->snap_share * (double)bud;
         if (whole) {
             c1 = c2 = A0.nt;
         } else if (!plan_checkpoints(A0.nt, m->opt.graph_steps, reuse ? A0.ckpt : m->opt.checkpoint_every,
