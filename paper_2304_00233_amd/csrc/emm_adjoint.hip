@@ -22,6 +22,7 @@
 #include "emm_adjoint.h"
 #include "emm_access.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace emm {
@@ -452,14 +453,16 @@ __global__ __launch_bounds__(AT) void adj_fold(const double *grad, double *out, 
     const int kk = b % nd2, c = b / nd2;
     const int j0 = jj == 0 ? r : jj + nbe, j1 = jj == nd1 - 1 ? n2 - 1 - r : jj + nbe;
     const int k0 = kk == 0 ? r : kk + nbe, k1 = kk == nd2 - 1 ? n3 - 1 - r : kk + nbe;
-    const int nj = j1 - j0 + 1, rows = nj * (k1 - k0 + 1);
-    const int side = nbe - r + 1;             // columns r .. nbe fold onto the first cell, as many onto the last
+    // (padding thinner than r: the outer input cells are off the update set)
+    const int nj = max(0, j1 - j0 + 1), rows = nj * max(0, k1 - k0 + 1);
+    const int side = max(0, nbe - r + 1);     // columns r .. nbe fold onto the first cell, as many onto the last
+    const int lo = min(r, nbe + 1);           // first column that is, or folds onto, an input cell
     double *o = out + (((long long)c * nd2 + kk) * nd1 + jj) * nd0;
     for (int s = 0; s < nsrc; ++s) {          // one source's fold after another, whatever the grouping
         const bool add = s > 0 || accumulate;
-        for (int i = r + threadIdx.x; i <= n1 - 1 - r; i += AT) {
+        for (int i = lo + threadIdx.x; i <= n1 - 1 - lo; i += AT) {
             const double *g = grad + ((long long)s * 3 + c) * fstride + i;
-            double acc = 0.0;
+            double acc = 0.0;                 // (the sums are zero off the update set)
 #pragma unroll 8
             for (int q = 0; q < rows; ++q) acc += g[(long long)(k0 + q / nj) * plane + (long long)(j0 + q % nj) * pitch];
             const int ii = i - nbe;
@@ -482,7 +485,7 @@ void launch_adj_fold(const double *grad, double *out, int nsrc, long long fstrid
                      int n1, int n2, int n3, int r, int nbe, int nd0, int nd1, int nd2, bool accumulate,
                      hipStream_t st) {
     const dim3 grid((unsigned)(3 * nd1 * nd2)), block(AT);
-    hipLaunchKernelGGL(adj_fold, grid, block, 2 * (nbe - r + 1) * sizeof(double), st, grad, out, nsrc, fstride, plane,
+    hipLaunchKernelGGL(adj_fold, grid, block, 2 * std::max(0, nbe - r + 1) * sizeof(double), st, grad, out, nsrc, fstride, plane,
                        pitch, n1, n2, n3, r, nbe, nd0, nd1, nd2, accumulate ? 1 : 0);
 }
 

@@ -1,6 +1,8 @@
-"""The gradient on a grid with very long x rows (a padded and an input row
-together exceed the LDS of a block) and few nodes across, against the FP64
-oracle's adjoint, and over two source groups against one (bit for bit)."""
+"""The fold of the padded gradient onto the input cells: very long x rows (a
+padded and an input row together exceed the LDS of a block) and few nodes
+across, and padding thinner than the stencil, whose outer input cells are
+never updated; against the FP64 oracle's adjoint, and over two source groups
+against one (bit for bit)."""
 import numpy as np
 import pytest
 
@@ -49,3 +51,24 @@ def test_gradient_on_very_long_rows(emm):
         with emm.Model(w, src_group=group) as m:
             out.append(m.gradient(g_bar=bar)[0])
     assert np.array_equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("rd,nb,ne", [(2, 0, 0), (2, 0, 1), (3, 1, 1), (1, 0, 0), (1, 0, 1), (4, 2, 1)])
+def test_gradient_with_padding_thinner_than_the_stencil(emm, rd, nb, ne):
+    w = configs.small_case(seed=71 + rd, shape=(21, 19, 18), rd=rd, nb=nb, ne=ne, nt=200, nsrc=2).with_(chan_mask=1)
+    print(f"[gpu] adjoint, thin padding {w.name} nb{nb} ne{ne}", flush=True)
+    s = np.float32(1.3)
+    st = F.make_setup(w, 2.0 * np.sqrt(max(w.freqs)))
+    G_obs, _ = F.forward(w.with_(rho11=w.rho11 * s, rho22=w.rho22 * s, rho33=w.rho33 * s), dt_override=st.dt)
+    _, g_o, _ = F.misfit_gradient(w, G_obs, frozen=st)
+    out = []
+    for group in (-1, 1):
+        with emm.Model(w, src_order=0, src_group=group) as m:
+            out.append(m.gradient(g_obs=G_obs)[0])
+    l2 = np.linalg.norm(out[0] - g_o) / np.linalg.norm(g_o)
+    print(f"[adjoint] {w.name}: rel L2 {l2:.2e}", flush=True)
+    assert l2 <= L2_TOL and np.array_equal(out[0], out[1])
+    off = np.ones(g_o.shape, bool)                   # input cells off the update set
+    m = rd - nb - ne
+    off[:, m:-m, m:-m, m:-m] = False
+    assert not np.any(out[0][off]) if m > 0 else True
