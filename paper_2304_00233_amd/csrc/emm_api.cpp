@@ -1484,7 +1484,9 @@ bool resident_ready(emm_model *m, hipStream_t stream, bool record, ResidentRun &
     const int L = 2 * m->r, ns = A.nsrc, ny = m->np[1] - L, nz = m->np[2] - L;
     emm::ResidentParams &X = run.X;
     // the grid rows under the receivers' stencils (all sources have the same
-    // receivers), the H channels' first, and each item's way to them
+    // receivers), the H channels' first, and each item's way to them (-1: a row
+    // off the update set, which no tile holds; a stencil reaches it where the
+    // padding is thinner than r, and the field is zero there)
     int per_step = 0;
     for (int h = 0; h < 2; ++h) {
         std::vector<emm::ResidentRow> &rows = m->row_h[h];
@@ -1495,6 +1497,10 @@ bool resident_ready(emm_model *m, hipStream_t stream, bool record, ResidentRun &
         X.nitems[h] = record ? (int)items.size() / (6 * ns) : 0;
         if (!X.nitems[h]) continue;
         std::vector<int> index((size_t)3 * m->np[1] * m->np[2], -1);
+        auto on_set = [&](const int *inf, int c, int b) {
+            const int y = inf[3] + b - m->r, z = inf[4] + c - m->r;
+            return y >= 0 && y < ny && z >= 0 && z < nz;
+        };
         auto at = [&](const int *inf, int c, int b) -> int & {
             return index[((size_t)inf[1] * m->np[2] + inf[4] + c) * m->np[1] + inf[3] + b];
         };
@@ -1502,6 +1508,7 @@ bool resident_ready(emm_model *m, hipStream_t stream, bool record, ResidentRun &
             const int *inf = &items[(size_t)6 * ns * q];
             for (int c = 0; c < L; ++c)
                 for (int b = 0; b < L; ++b) {
+                    if (!on_set(inf, c, b)) continue;
                     int &id = at(inf, c, b);
                     if (id < 0) {
                         id = (int)rows.size();
@@ -1534,6 +1541,10 @@ bool resident_ready(emm_model *m, hipStream_t stream, bool record, ResidentRun &
             const int *inf = &items[(size_t)6 * ns * q];
             for (int c = 0; c < L; ++c)
                 for (int b = 0; b < L; ++b) {
+                    if (!on_set(inf, c, b)) {
+                        way.push_back(-1);
+                        continue;
+                    }
                     const emm::ResidentRow &w = rows[at(inf, c, b)];
                     way.push_back(w.off + inf[2] - w.x0);
                 }

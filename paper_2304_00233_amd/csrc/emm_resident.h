@@ -34,7 +34,8 @@ struct ResidentParams {
     float *samples;
     int nbase, per_step;
     // items of one source (item q of the source is item q * nsrc + src of
-    // its list): offset of the samples of stencil row (c, b), [item][(2r)^2]
+    // its list): offset of the samples of stencil row (c, b), [item][(2r)^2],
+    // -1 for a row off the update set (zeros)
     const int *item_rows[2];
     int nitems[2];
     float *snap;                      // not null: E after step n also goes to snap + (n - n0) * snap_stride

@@ -450,7 +450,10 @@ __global__ __launch_bounds__(256) void resident_sum(const StepParams pe, const S
     const float *s = x.samples + (long long)(n - x.nbase) * x.per_step;
     const int *row = x.item_rows[h] + mine * (L * L);
     const double v = rec_sum<R>(P.item_w + 3 * L * (mine * P.nsrc + x.src), threadIdx.x & 63,
-                                [&](int, int a, int b, int c) { return s[row[c * L + b] + a]; });
+                                [&](int, int a, int b, int c) {
+                                    const int at = row[c * L + b];
+                                    return at < 0 ? 0.f : s[at + a];
+                                });
     if ((threadIdx.x & 63) == 0) u[(long long)(n - x.nbase) * nit + it] = v;
 }
 

@@ -12,7 +12,9 @@ CSRC = os.path.join(ROOT, "paper_2304_00233_amd", "csrc")
 
 # (shape, rd, nb, ne) -> planes per thread, one thread group or several
 GRIDS = [((37, 29, 23), 2, 10, 7, 3, False), ((21, 45, 64), 2, 10, 8, 4, False), ((26, 44, 55), 1, 10, 8, 4, True),
-         ((25, 40, 82), 3, 6, 8, 3, True), ((48, 48, 48), 2, 10, 7, 5, False), ((9, 60, 40), 1, 3, 2, 1, True)]
+         ((25, 40, 82), 3, 6, 8, 3, True), ((48, 48, 48), 2, 10, 7, 5, False), ((9, 60, 40), 1, 3, 2, 1, True),
+         # one update plane (two per thread where that lets it receive more words)
+         ((61, 42, 5), 2, 0, 0, 2, False), ((45, 58, 7), 3, 0, 0, 2, False)]
 
 PROGRAM = r"""
 #include "emm_resident_plan.h"
