@@ -242,9 +242,11 @@ emm_status emm_query(const emm_model *m, emm_info *info);
  * without airwave, converge_tol, profile, fused and any launch option (tile_kz
  * > 0, tile_x, tile_rows, nontemporal, src_order, ce_table) set: setting one,
  * to any value but its default, selects the half-step launches.  The results
- * are the same bit for bit.  A resident loop whose launch is refused, or whose
- * blocks wait for each other for more than 2 s, is run again as half-step
- * launches, which the model then keeps to.  info.resident tells which ran.
+ * are the same bit for bit.  A resident loop whose launch is refused (another
+ * process holds the device's cooperative queue), or whose blocks wait for each
+ * other for more than 2 s, is run again as half-step launches, which the model
+ * then keeps to; after a refusal no model of the process tries on that device
+ * for 10 s.  info.resident tells which ran.
  * hip_stream: a hipStream_t to run on, or NULL for the library's own stream.
  * Errors: ARG, GEOMETRY, FREQ, NONFINITE, OOM, DEVICE. */
 emm_status emm_forward(emm_model *m, const emm_source *src, int nsrc,

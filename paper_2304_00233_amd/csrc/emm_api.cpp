@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <complex>
 #include <cstdint>
@@ -67,6 +68,28 @@ hipError_t scratch_address(int device, void **ptr) {
     }
     *ptr = slot.ptr;
     return slot.err;
+}
+
+// The cooperative queue of a device is one process's at a time.  A launch that
+// finds it taken fails only after some 80 ms, in which the runtime sets up and
+// tears down a queue and the holder's work stands still as well (40 forwards
+// of 4 ms each in two processes at once: 950 and 1200 ms when every new model
+// tries, 340 each without).  After a refusal no model tries on that device for
+// a while; the half-step launches give the same results.
+constexpr double kRefusalSeconds = 10.0;
+std::mutex g_refused_mu;
+std::map<int, std::chrono::steady_clock::time_point> g_refused_until;
+
+void note_refusal(int device, double seconds) {
+    std::lock_guard<std::mutex> lock(g_refused_mu);
+    g_refused_until[device] = std::chrono::steady_clock::now() +
+                              std::chrono::duration_cast<std::chrono::steady_clock::duration>(
+                                  std::chrono::duration<double>(seconds));
+}
+bool refused_lately(int device) {
+    std::lock_guard<std::mutex> lock(g_refused_mu);
+    const auto it = g_refused_until.find(device);
+    return it != g_refused_until.end() && std::chrono::steady_clock::now() < it->second;
 }
 
 }  // namespace
@@ -1467,7 +1490,7 @@ bool resident_wanted(const emm_model *m, int nsrc) {
     const emm_options &o = m->opt;
     return m->res.gy > 0 && nsrc <= (m->res.planes == 1 ? 2 : 1) && !o.airwave && !(o.converge_tol > 0.0) &&
            !o.profile && !o.fused && o.tile_kz <= 0 && o.tile_x == 0 && o.tile_rows == 0 && o.nontemporal < 0 &&
-           o.src_order < 0 && o.ce_table < 0;
+           o.src_order < 0 && o.ce_table < 0 && !refused_lately(m->device);
 }
 
 // What a resident run of the prepared acquisition needs beside the state.
@@ -1613,8 +1636,8 @@ bool resident_ready(emm_model *m, hipStream_t stream, bool record, ResidentRun &
 
 // Steps [n0, n1) of every source of the prepared acquisition, from the state
 // arrays and back to them.  snap: E after step n also goes to snap slot
-// n - n0.  false: a launch was refused (cooperative queues are one process's
-// at a time on a device); the model goes step by step from then on.
+// n - n0.  false: a launch was refused; the model goes step by step from then
+// on.
 bool resident_steps(emm_model *m, hipStream_t stream, ResidentRun &run, int n0, int n1, float *snap) {
     const Acq &A = m->acq;
     emm::ResidentParams &X = run.X;
@@ -1630,6 +1653,7 @@ bool resident_steps(emm_model *m, hipStream_t stream, ResidentRun &run, int n0, 
             if (m->res_limits.launches > 0) --m->res_limits.launches;
             if (!granted || emm::launch_resident(m->r, m->res, A.Pe, A.Ph, X, stream) != hipSuccess) {
                 (void)hipGetLastError();
+                if (granted) note_refusal(m->device, kRefusalSeconds);
                 m->res.gy = 0;
                 return false;
             }
@@ -2136,6 +2160,12 @@ emm_status emm_test_resident(emm_model *m, double patience_s, int launches) {
     if (!m || !(patience_s >= 0.0)) return fail(m, EMM_ERR_ARG, "bad resident limits");
     m->res_limits.patience = (unsigned long long)(patience_s * 1e8);
     m->res_limits.launches = launches;
+    return EMM_OK;
+}
+
+// As if the device had refused a cooperative launch and would for so long.
+emm_status emm_test_refusal(int device, double seconds) {
+    note_refusal(device, seconds);
     return EMM_OK;
 }
 

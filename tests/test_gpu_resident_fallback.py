@@ -103,3 +103,18 @@ def test_autotuned_where_the_launches_run(emm, w, ref):
         assert np.array_equal(m.forward(), ref[0]) and m.info()["resident"] > 0
         assert emm._lib.emm_test_tuned(m.h) == 1
         assert np.array_equal(m.gradient(g_bar=BAR)[0], ref[1])
+
+
+def test_no_model_tries_for_a_while_after_a_refusal(emm, w, ref):
+    emm._lib.emm_test_refusal.argtypes = [C.c_int, C.c_double]
+    print("[gpu] resident loops after a refusal by the device", flush=True)
+    try:
+        assert emm._lib.emm_test_refusal(0, 100.0) == 0
+        for _ in range(2):
+            with emm.Model(w) as m:
+                assert np.array_equal(m.forward(), ref[0]) and m.info()["resident"] == 0
+                assert np.array_equal(m.gradient(g_bar=BAR)[0], ref[1])
+    finally:
+        emm._lib.emm_test_refusal(0, 0.0)
+    with emm.Model(w) as m:
+        assert np.array_equal(m.forward(), ref[0]) and m.info()["resident"] > 0
