@@ -801,11 +801,10 @@ emm_status check_source(emm_model *m, const emm_source &S) {
         !std::isfinite(S.y) || !std::isfinite(S.z))
         return fail(m, EMM_ERR_ARG, "source component must be 0..2 with a finite non-zero moment");
     const double p[3] = {S.x, S.y, S.z};
-    const int L = 2 * m->r;
     for (int a = 0; a < 3; ++a) {
         double w[2 * emm::kMaxR];
-        const int base = emm::point_stencil(a == S.comp ? m->half[a] : m->axes[a], p[a], m->r, w);
-        if (!(base >= m->nbe && base + L - 1 <= m->np[a] - 1 - m->nbe))
+        const std::vector<double> &c = a == S.comp ? m->half[a] : m->axes[a];
+        if (!emm::stencil_inside(c, emm::point_stencil(c, p[a], m->r, w), m->r, m->np[a], m->nbe))
             return fail(m, EMM_ERR_GEOMETRY, "source stencil leaves the interior");
     }
     return EMM_OK;
@@ -858,7 +857,6 @@ emm_status prepare(emm_model *m, const emm_source *src, int nsrc, const emm_rece
         if (chan_mask >> c & 1u) A.chans.push_back(c);
     const int nch = (int)A.chans.size();
     auto coords = [&](int a, int h) -> const std::vector<double> & { return h ? m->half[a] : m->axes[a]; };
-    auto inside = [&](int a, int base) { return base >= m->nbe && base + L - 1 <= m->np[a] - 1 - m->nbe; };
 
     // sources: (2r)^3 stencil on the E_comp grid, J = moment w / V, scaled to max |q| = 1
     std::vector<int> sinfo(4 * nsrc);
@@ -875,11 +873,8 @@ emm_status prepare(emm_model *m, const emm_source *src, int nsrc, const emm_rece
         // control volume: primal interval along comp, dual intervals across
         double ext[3][2 * emm::kMaxR];
         for (int a = 0; a < 3; ++a)
-            for (int q = 0; q < L; ++q) {
-                const int idx = base[a] + q;
-                ext[a][q] = a == S.comp ? m->axes[a][idx + 1] - m->axes[a][idx]
-                                        : m->half[a][idx] - m->half[a][idx - 1];
-            }
+            for (int q = 0; q < L; ++q)
+                ext[a][q] = emm::source_extent(m->axes[a], m->half[a], base[a] + q, a == S.comp);
         std::vector<double> qd(L3);
         double qmax = 0.0;
         for (int c = 0; c < L; ++c)
@@ -910,8 +905,9 @@ emm_status prepare(emm_model *m, const emm_source *src, int nsrc, const emm_rece
             double w[3][2 * emm::kMaxR];
             int base[3];
             for (int a = 0; a < 3; ++a) {
-                base[a] = emm::point_stencil(coords(a, kStag[ch][a]), p[a], r, w[a]);
-                if (!inside(a, base[a])) return fail(m, EMM_ERR_GEOMETRY, "receiver stencil leaves the interior");
+                const std::vector<double> &on = coords(a, kStag[ch][a]);
+                base[a] = emm::point_stencil(on, p[a], r, w[a]);
+                if (!emm::stencil_inside(on, base[a], r, m->np[a], m->nbe)) return fail(m, EMM_ERR_GEOMETRY, "receiver stencil leaves the interior");
             }
             std::vector<int> &inf = ch < 3 ? A.items_hstep : A.items_estep;
             std::vector<float> &wv = ch < 3 ? A.w_hstep : A.w_estep;

@@ -115,6 +115,18 @@ int point_stencil(const std::vector<double> &coords, double p, int r, double *w)
     return base;
 }
 
+bool stencil_inside(const std::vector<double> &coords, int base, int r, int n, int nbe) {
+    return base >= nbe && base + 2 * r - 1 <= n - 1 - nbe && base + 2 * r <= static_cast<int>(coords.size());
+}
+
+double source_extent(const std::vector<double> &axis, const std::vector<double> &half, int i, bool along) {
+    const int n = static_cast<int>(axis.size());
+    if (along) return axis[i + 1] - axis[i];
+    const double lo = i > 0 ? half[i - 1] : axis[0] - 0.5 * (axis[1] - axis[0]);
+    const double hi = i < n - 1 ? half[i] : axis[n - 1] + 0.5 * (axis[n - 1] - axis[n - 2]);
+    return hi - lo;
+}
+
 std::vector<double> wavelet(int nt, double dt, double fp) {
     const double pi = 3.14159265358979323846;
     const double tau = 1.0 / (pi * fp);

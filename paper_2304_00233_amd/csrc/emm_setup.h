@@ -37,6 +37,16 @@ CpmlAxis cpml_axis(const std::vector<double> &xp, int nb, double dt, double v_lo
 // range: the caller validates) and fills w[2r].
 int point_stencil(const std::vector<double> &coords, double p, int r, double *w);
 
+// Whether a 2r-point stencil on `coords` starting at base lies on the axis and
+// in the interior of its n padded nodes, nbe from each end (an unpadded axis
+// has no half node after its last node).
+bool stencil_inside(const std::vector<double> &coords, int base, int r, int n, int nbe);
+
+// Extent of the control volume of node i of an axis: along the source's
+// component the primal interval after it, across it the dual interval (at the
+// ends of the axis as if it went on with its end interval).
+double source_extent(const std::vector<double> &axis, const std::vector<double> &half, int i, bool along);
+
 // Wavelet samples at half steps s_n = s((n+1/2) dt) with
 // s(t) = -((t - 4 tau)/tau) exp(-((t - 4 tau)/tau)^2), tau = 1/(pi fp).
 std::vector<double> wavelet(int nt, double dt, double fp);
