@@ -327,13 +327,14 @@ int choose_kz(const emm_model *m, int xt, int yt, int nsrc) {
     return (int)((nzv + zc - 1) / zc);
 }
 
-// Nontemporal hints when the arrays one step touches (fields of all sources
-// and dt/eps) exceed 160 MiB, well inside the 256 MB Infinity Cache below
-// that, but not for a batch in the source-slowest order (choose_sorder): 8
-// sources at r = 4 on 400 x 400 x 200 nodes take 6031 us a step without and
-// 6275 with hints, 4 at r = 2 on 256^3 1588 and 1612; two sources on 200 x
-// 200 x 100 at r = 4 316 without and 293 with.  The autotuner overrides this
-// with a measurement.
+// Nontemporal hints for up to three sources when the arrays one step touches
+// (fields of all sources and dt/eps) exceed 160 MiB, well inside the 256 MB
+// Infinity Cache below that: two sources on 200 x 200 x 100 at r = 4 take 316 us
+// a step without and 293 with.  Not from four sources on: 8 at r = 4 on 400 x
+// 400 x 200 nodes 6031 without and 6275 with, 4 at r = 2 on 256^3 1588 and 1612
+// (both in the source-slowest order that choose_sorder gives them; with
+// src_order = 0 forced the rule is the same).  The autotuner overrides this with
+// a measurement.
 int choose_stream(const emm_model *m, long long fstride, int nsrc) {
     if (m->opt.nontemporal >= 0) return m->opt.nontemporal;
     if (m->opt.tile_kz < 0) {

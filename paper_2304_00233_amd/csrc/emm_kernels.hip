@@ -100,13 +100,17 @@ __device__ void rec_dft(const StepParams &p, int blk, const float *F0,
 //
 // Beyond the caches memory bounds it (a plain march over the same arrays with
 // no halo takes 370 us per E step on the 438 x 438 x 238 padded grid, this
-// kernel 382 per source of eight); on smaller grids the vector unit does: a
-// plane's 24 (r = 2) to 57 (r = 4) FMAs came with 116-160 other vector
+// kernel 382 per source of eight).  On grids that the Infinity Cache feeds the
+// march reaches 6.3 TB/s (162 x 162 x 130 padded cells 21.7 us, the E step 26.9
+// with its CPML memories, a seventh of its bytes).
+// A plane's 24 (r = 2) to 57 (r = 4) FMAs came with 116-160 other vector
 // instructions, mostly 64-bit addresses, queue shifts and bounds checks.
 // Scalar plane bases, queues that turn by renaming and halo elements clamped
-// into the array instead of branched over leave 43-78.  Per E + H step at
-// the same tiles: 8 sources at r = 4 on 400 x 400 x 200 nodes 6360 -> 6031
-// us, 128 x 128 x 96 at 9 planes per block 67 -> 56, 48^3 at 9 29.6 -> 23.8.
+// into the array instead of branched over leave 43-78.  That pays where a
+// block has many planes and few blocks share a unit, per E + H step: 48^3 at 9
+// planes per block 29.6 -> 23.8 us, 128 x 128 x 96 at 9 67 -> 56, 8 sources at
+// r = 4 on 400 x 400 x 200 nodes 6360 -> 6031; at the short chunks that 128 x
+// 128 x 96 takes by default it does not (E 27.1 -> 26.9).
 //
 // CI (E step only): dt/eps comes from the compact form, one index word per
 // cell (4 bytes instead of 12) into a table of the model's distinct values,

@@ -78,7 +78,8 @@ __global__ __launch_bounds__(resident_threads(P)) void resident_kernel(const Ste
     constexpr int HE = R - 1, HH = R;         // halo below of the tiles of E (read with D+) and H (D-)
     __shared__ float lds[6 * kResSlot];
     __shared__ float ztab[2][kResTall][L + 2];
-    __shared__ int2 rowlist[2][kResRows];     // sampled rows: LDS offset | length << 16 | component << 28, sample offset
+    __shared__ int2 rowlist[2][kResRows];     // sampled rows: offset in the field's three tiles | length << 16, sample offset
+    static_assert(3 * kResSlot <= 65536, "offsets in a field's tiles take 16 bits (rowlist, wto)");
     __shared__ int nrow[2], s_stuck;
     const int n1 = pe.n1, n2 = pe.n2, n3 = pe.n3, pitch = pe.pitch, nb = pe.nb, nb2 = 2 * pe.nb;
     const int plane = (int)pe.plane;

@@ -15,8 +15,9 @@ def emm():
     return m
 
 
-# shape, rd, nb, ne, sources: tiles of uneven rows and planes, one to five
-# planes per thread, no CPML, a single tile row, the smallest grids
+# shape, rd, nb, ne, sources: tiles of uneven rows and planes, one plane per
+# thread and (48^3) five, no CPML, the smallest grids; the plans between are in
+# test_gpu_resident_plans.py
 CASES = [((30, 26, 22), 2, 6, 4, 1), ((37, 29, 23), 1, 10, 6, 1), ((48, 48, 48), 2, 10, 7, 1),
          ((48, 48, 48), 1, 10, 6, 1), ((21, 19, 33), 3, 5, 4, 1), ((14, 15, 13), 2, 0, 3, 2),
          ((70, 12, 11), 2, 4, 3, 2), ((9, 60, 40), 1, 3, 2, 1), ((33, 9, 50), 3, 2, 3, 2)]
