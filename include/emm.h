@@ -263,7 +263,8 @@ emm_status emm_forward(emm_model *m, const emm_source *src, int nsrc,
  * hipMalloc / hipFree, creates no event or graph, and clears what must start
  * at zero with a fill kernel.  It runs every source in one time loop,
  * resident where emm_forward's would be (graph_steps and profile are ignored
- * for the call) and the workspace has room, else direct launches (tiles: the
+ * for the call; the HIP runtime sets up its cooperative queue at a process's
+ * first) and the workspace has room, else direct launches (tiles: the
  * model's option or earlier autotuned choice, no autotuning).  A call
  * whose buffers exceed 128 MiB fails with EMM_ERR_OOM and a message giving
  * the bytes it needs (about 30 MB per source on a 48^3 grid with 10 CPML

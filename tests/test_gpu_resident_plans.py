@@ -70,3 +70,27 @@ def test_profiled_gradient_with_every_step_kept(emm):
         assert np.array_equal(g, ref) and i["resident"] == 0
         assert i["e_launches"] == i["h_launches"] == 4
         assert 0 < i["e_kernel_ms"] < i["forward_ms"] and 0 < i["h_kernel_ms"] < i["forward_ms"]
+
+
+def test_resident_loops_of_several_threads(emm):
+    """One model per thread, each on its own stream: cooperative launches take
+    turns, half-step launches of other threads run beside them."""
+    import threading
+    w = configs.small_case(seed=5, shape=(30, 28, 26), nt=80)
+    with emm.Model(w, src_order=0) as m:
+        ref = m.forward()
+    got = []
+
+    def work(opt):
+        with emm.Model(w, **opt) as m:
+            for _ in range(4):
+                got.append((np.array_equal(m.forward(), ref), m.info()["resident"] > 0))
+
+    print("[gpu] resident loops of three threads beside one of launches", flush=True)
+    threads = [threading.Thread(target=work, args=(opt,)) for opt in ({}, {}, {}, dict(src_order=0))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert len(got) == 16 and all(same for same, _ in got)
+    assert sum(resident for _, resident in got) == 12
